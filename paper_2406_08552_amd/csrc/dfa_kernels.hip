@@ -268,6 +268,25 @@ struct QFrag {
     bf16x8 t[QB];   // dims D32.. in lane rows g < TAIL/8, zero elsewhere
 };
 
+// Q fragments (B operand of S^T = K Q^T), zero beyond L and beyond d
+template <int D, int QB>
+__device__ __forceinline__ void load_q(QFrag<D, QB>& q, const uint16_t* __restrict__ Qbh, int qw0, int L, int r, int g) {
+    using G = Geo<D>;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int qrow = qw0 + 16 * qb + r;
+        const bool ok = qrow < L;
+        const uint16_t* qp = Qbh + (size_t)(ok ? qrow : 0) * D;
+#pragma unroll
+        for (int c = 0; c < G::NC32; ++c)
+            q.a[qb][c] = as_bf16x8(ok ? *(const u32x4*)(qp + 32 * c + 8 * g) : u32x4{0u, 0u, 0u, 0u});
+        q.t[qb] = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
+        if constexpr (G::TAIL > 0) {
+            if (ok && 8 * g < G::TAIL) q.t[qb] = as_bf16x8(*(const u32x4*)(qp + G::D32 + 8 * g));
+        }
+    }
+}
+
 // Score tile S^T for the wavefront's 16 * QB queries against the 64 keys of one LDS
 // stage: S[qb][kb][i] is the score of query (16*qb + lane%16) and key
 // (16*kb + 4*(lane/16) + i) of the tile.
@@ -678,6 +697,18 @@ struct Walk {
         }
     }
 
+    // A tile of a window walk in two forms, masked (which also cuts keys beyond
+    // L) and plain: fewer registers than the three of a band segment.
+    __device__ __forceinline__ void tile_window(Acc<D, QB>& acc, const QFrag<D, QB>& q, const uint16_t* Ks,
+                                                const uint16_t* Vs, int k0) {
+        const int cls = classify(k0);
+        if (cls == TILE_OUTSIDE) return;
+        Tile<QB> S;
+        score_tile<D>(Ks, q, S, r, g);
+        if (cls == TILE_BOUNDARY || k0 + BK > L) accumulate<D, MASK_BAND_IN>(acc, S, Vs, r, g, qw0, k0, L, w, c);
+        else accumulate<D, MASK_NONE>(acc, S, Vs, r, g, qw0, k0, L, w, c);
+    }
+
     // One update with the score tile S of the tile at k0.  With F, an unmasked
     // tile takes the fast form once every query of the wavefront has a running
     // max, and the exact form before that and when the fast form finds a
@@ -734,6 +765,42 @@ struct Walk {
 template <int KMODE>
 constexpr bool split_refresh() { return KMODE == MODE_REFRESH_SPLIT; }
 
+// Epilogue of a two-accumulator refresh: W = aw / lw, O from both, each scaled
+// from its own running max to the larger one, R = O - W.
+template <int D, int QB>
+__device__ __forceinline__ void store_split(const Params& p, const Acc<D, QB>& aw, const Acc<D, QB>& ax, size_t head_off,
+                                            int qw0, int L, int r, int g) {
+    using G = Geo<D>;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int qrow = qw0 + 16 * qb + r;
+        // row sums first: they exchange values across lanes
+        const float lw = row_sum<D>(aw, qb, r), lx = row_sum<D>(ax, qb, r);
+        const bool has_x = ax.thr[qb] != NEG_INF;
+        const float mw = aw.running_max(qb);
+        const float mx = ax.running_max(qb);
+        const float mm = fmaxf(mw, mx);
+        const float sw = has_x ? __builtin_amdgcn_exp2f(mw - mm) : 1.f;
+        const float sx = has_x ? __builtin_amdgcn_exp2f(mx - mm) : 0.f;
+        const float invw = 1.f / lw;
+        const float inv = 1.f / (lw * sw + lx * sx);
+        if (qrow >= L) continue;
+        const size_t row_off = head_off + (size_t)qrow * D;
+#pragma unroll
+        for (int mb = 0; mb < G::NDB; ++mb) {
+#pragma clang fp contract(off)
+            const int col = 16 * mb + 4 * g;
+            if (col >= D) continue;
+            const size_t off = row_off + col;
+            const f32x4 wv = aw.o[qb][mb] * invw;
+            const f32x4 o = has_x ? (aw.o[qb][mb] * sw + ax.o[qb][mb] * sx) * inv : wv;
+            *(f32x4*)(p.Rout + off) = o - wv;
+            const u32x2 ov = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+            for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + off) = ov;
+        }
+    }
+}
+
 // Refresh in one pass (Sec. 3.2, Eq. 1), for short sequences: W = aw / lw from the in-band scores
 // alone; O combines both accumulators, each scaled from its own running max
 // to the larger one.  A query whose band covers every key has no
@@ -749,36 +816,7 @@ __device__ __forceinline__ void refresh_split(const Params& p, uint16_t* smem, W
     wait_vm_all();
     __syncthreads();
     wk.run_split(aw, ax, q, 0, ntiles);
-    if (!wk.wave_active) return;
-    const int r = wk.r, g = wk.g;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int qrow = wk.qw0 + 16 * qb + r;
-        // row sums first: they exchange values across lanes
-        const float lw = row_sum<D>(aw, qb, r), lx = row_sum<D>(ax, qb, r);
-        const bool has_x = ax.thr[qb] != NEG_INF;
-        const float mw = aw.running_max(qb);
-        const float mx = ax.running_max(qb);
-        const float mm = fmaxf(mw, mx);
-        const float sw = has_x ? __builtin_amdgcn_exp2f(mw - mm) : 1.f;
-        const float sx = has_x ? __builtin_amdgcn_exp2f(mx - mm) : 0.f;
-        const float invw = 1.f / lw;
-        const float inv = 1.f / (lw * sw + lx * sx);
-        if (qrow >= wk.L) continue;
-        const size_t row_off = head_off + (size_t)qrow * D;
-#pragma unroll
-        for (int mb = 0; mb < G::NDB; ++mb) {
-#pragma clang fp contract(off)
-            const int col = 16 * mb + 4 * g;
-            if (col >= D) continue;
-            const size_t off = row_off + col;
-            const f32x4 wv = aw.o[qb][mb] * invw;
-            const f32x4 o = has_x ? (aw.o[qb][mb] * sw + ax.o[qb][mb] * sx) * inv : wv;
-            *(f32x4*)(p.Rout + off) = o - wv;
-            const u32x2 ov = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
-            for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + off) = ov;
-        }
-    }
+    if (wk.wave_active) store_split<D, QB>(p, aw, ax, head_off, wk.qw0, wk.L, wk.r, wk.g);
 }
 
 template <int D, int KMODE, int QB>
@@ -823,21 +861,8 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
         }
     }
 
-    // Q fragments (B operand of S^T = K Q^T), zero beyond L and beyond d
     QFrag<D, QB> q;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int qrow = qw0 + 16 * qb + r;
-        const bool ok = qrow < L;
-        const uint16_t* qp = Qbh + (size_t)(ok ? qrow : 0) * D;
-#pragma unroll
-        for (int c = 0; c < G::NC32; ++c)
-            q.a[qb][c] = as_bf16x8(ok ? *(const u32x4*)(qp + 32 * c + 8 * g) : u32x4{0u, 0u, 0u, 0u});
-        q.t[qb] = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
-        if constexpr (G::TAIL > 0) {
-            if (ok && 8 * g < G::TAIL) q.t[qb] = as_bf16x8(*(const u32x4*)(qp + G::D32 + 8 * g));
-        }
-    }
+    load_q<D, QB>(q, Qbh, qw0, L, r, g);
 
     // the fast update measured 1-2% faster in the long walks of two query
     // blocks per wavefront and about 1% slower in the short walks of one
@@ -1007,6 +1032,172 @@ __global__ void __launch_bounds__(NTHREADS)
     attn_body<D, MODE, QB>(p, smem);
 }
 
+// ---------------------------------------------------------------------------
+// Launches that leave SIMDs short of wavefronts: the key tiles of a 64-query
+// workgroup are dealt to KS groups of four wavefronts, each with LDS stages, a
+// running maximum and accumulators of its own, and group 0 combines them.  At
+// one wavefront per SIMD a tile costs its whole dependence chain (scores, exp,
+// PV: 0.64 us), several times its issue time; deeper copy pipelines did not
+// help there.
+// ---------------------------------------------------------------------------
+
+// One query block's state as a wavefront leaves it in LDS: 16 bytes per lane
+// and output block, then (-m - P_SHIFT, threshold, row-sum share).
+// Wavefronts per SIMD that its register budget allows for.
+template <int KMODE, int KS>
+constexpr int keysplit_waves() { return KMODE == MODE_REFRESH ? KS : 4; }
+
+template <int D>
+constexpr int state_elems() { return (Geo<D>::NDB + 1) * 64 * 8; }
+
+template <int D>
+__device__ __forceinline__ void put_state(const Acc<D, 1>& a, uint16_t* at, int lane) {
+#pragma unroll
+    for (int mb = 0; mb < Geo<D>::NDB; ++mb) *(f32x4*)(at + (mb * 64 + lane) * 8) = a.o[0][mb];
+    *(f32x4*)(at + (Geo<D>::NDB * 64 + lane) * 8) = f32x4{a.negm[0], a.thr[0], a.l[0], 0.f};
+}
+
+// a += the state at `at`, both scaled to the larger running maximum
+template <int D>
+__device__ __forceinline__ void add_state(Acc<D, 1>& a, const uint16_t* at, int lane, float c) {
+    const f32x4 st = *(const f32x4*)(at + (Geo<D>::NDB * 64 + lane) * 8);
+    if (__all(st[1] == NEG_INF)) return;   // it saw no key of these queries
+    const float ma = a.running_max(0), mb_ = st[1] == NEG_INF ? NEG_INF : -(st[0] + P_SHIFT);
+    const float m = fmaxf(ma, mb_);
+    const float sa = ma == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(ma - m);
+    const float sb = mb_ == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(mb_ - m);
+#pragma unroll
+    for (int mb = 0; mb < Geo<D>::NDB; ++mb) a.o[0][mb] = a.o[0][mb] * sa + *(const f32x4*)(at + (mb * 64 + lane) * 8) * sb;
+    a.l[0] = a.l[0] * sa + st[2] * sb;
+    if (m != NEG_INF) {
+        a.negm[0] = -m - P_SHIFT;
+        a.thr[0] = (m + RESCALE_THRESH) / c;
+    }
+}
+
+template <int D, int KMODE, int KS>
+__global__ void __launch_bounds__(NTHREADS* KS) __attribute__((amdgpu_waves_per_eu(keysplit_waves<KMODE, KS>(), keysplit_waves<KMODE, KS>())))
+attn_keysplit_kernel(Params p) {
+    using G = Geo<D>;
+    constexpr int MODE = KMODE == MODE_ASC ? MODE_FULL : KMODE;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[KS * 2 * G::STAGE_ELEMS];
+    // states of groups 1 .. KS - 1: behind group 0's stages (which may hold
+    // residual rows), or from the start for a refresh's two accumulators
+    constexpr int NACC = MODE == MODE_REFRESH ? 2 : 1, STATE0 = MODE == MODE_REFRESH ? 0 : 2 * G::STAGE_ELEMS;
+    constexpr int STATES = NWAVES * state_elems<D>();
+    static_assert(STATE0 + (KS - 1) * NACC * STATES <= KS * 2 * G::STAGE_ELEMS, "the states must fit the stages");
+    static_assert(bq<1>() * D * 4 <= G::STAGE_ELEMS * 2, "residual rows must fit one LDS stage");
+    const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NTHREADS);
+    const int tid = threadIdx.x % NTHREADS;
+    const int lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+    uint16_t* sg = smem + grp * 2 * G::STAGE_ELEMS;    // the group's stages
+
+    int blk = blockIdx.x;
+    if ((p.nblocks & 7) == 0) blk = (blk & 7) * (p.nblocks >> 3) + (blk >> 3);
+    const int bh = blk / p.n_qt, qt = blk % p.n_qt;
+    const int L = p.L, w = p.w;
+    const size_t head_off = (size_t)bh * L * D;
+    const int q0 = qt * bq<1>(), qw0 = q0 + wave * 16;
+
+    if constexpr (G::ONES) {
+        for (int idx = tid; idx < 2 * BK * 8; idx += NTHREADS) {
+            const int st = idx / (BK * 8), row = (idx / 8) % BK, e = idx % 8;
+            sg[st * G::STAGE_ELEMS + G::KS_ELEMS + row * G::VP + D + e] = (e == 0) ? (uint16_t)0x3F80u : (uint16_t)0u;
+        }
+    }
+    Walk<D, 1> wk;
+    wk.Kbh = p.K + head_off;
+    wk.Vbh = p.V + head_off;
+    wk.smem = sg;
+    wk.tid = tid;
+    wk.r = r;
+    wk.g = g;
+    wk.L = L;
+    wk.w = w;
+    wk.qw0 = qw0;
+    wk.qhi_w = min(qw0 + 15, L - 1);
+    wk.wave_active = qw0 < L;
+    wk.c = p.c;
+    wk.stage = 0;
+    wk.rpre = nullptr;
+
+    // tiles [t0, t1) of the walk, tile t0 + i KS + grp for group grp
+    int t0 = 0, t1 = (L + BK - 1) / BK;
+    if constexpr (MODE == MODE_WINDOW) {
+        t0 = (int)(max(0LL, (long long)q0 - w) / BK);
+        t1 = (int)(min((long long)L - 1, (long long)min(q0 + bq<1>() - 1, L - 1) + w) / BK) + 1;
+    }
+    const int iters = (t1 - t0 + KS - 1) / KS;
+    t0 += grp;
+    if (t0 < t1) issue_tile<D>(wk.Kbh, wk.Vbh, t0 * BK, L, tid, sg, sg + G::KS_ELEMS);
+
+    QFrag<D, 1> q;
+    load_q<D, 1>(q, p.Q + head_off, qw0, L, r, g);
+    Acc<D, 1> acc, ax;
+    acc.init();
+    ax.init();
+    wait_vm_all();
+    __syncthreads();
+    for (int i = 0; i < iters; ++i) {
+        const int t = t0 + i * KS;
+        const uint16_t* Ks = sg + (i & 1) * G::STAGE_ELEMS;
+        const uint16_t* Vs = Ks + G::KS_ELEMS;
+        uint16_t* nx = sg + (~i & 1) * G::STAGE_ELEMS;
+        if (t + KS < t1) issue_tile<D>(wk.Kbh, wk.Vbh, (t + KS) * BK, L, tid, nx, nx + G::KS_ELEMS);
+        else if (MODE == MODE_WINDOW && grp == 0 && i == iters - 1 && p.Rin)
+            // the residual rows, into the stage that the last tile leaves free
+            issue_rows<bq<1>() * D / 4>(p.Rin + head_off + (size_t)q0 * D, (min(L, q0 + bq<1>()) - q0) * D / 4, tid, nx);
+        if (t < t1 && wk.wave_active) {
+            if constexpr (MODE == MODE_REFRESH) wk.tile_split(acc, ax, q, Ks, Vs, t * BK);
+            else if constexpr (MODE == MODE_WINDOW) wk.tile_window(acc, q, Ks, Vs, t * BK);
+            else if (t * BK + BK <= L) wk.template tile<SEG_PLAIN, false>(acc, q, Ks, Vs, t * BK);
+            // the ragged last tile (its group's last, in the last iteration) follows the loop
+        }
+        wait_vm_all();
+        __syncthreads();
+    }
+    if constexpr (MODE == MODE_FULL) {
+        const int i = iters - 1, t = t0 + i * KS;
+        if (t < t1 && wk.wave_active && t * BK + BK > L) {
+            const uint16_t* Ks = sg + (i & 1) * G::STAGE_ELEMS;
+            wk.template tile<SEG_KEYS, false>(acc, q, Ks, Ks + G::KS_ELEMS, t * BK);
+        }
+        __syncthreads();
+    }
+    uint16_t* states = smem + STATE0 + wave * state_elems<D>();
+    if (grp != 0) {
+        put_state<D>(acc, states + (grp - 1) * NACC * STATES, lane);
+        if constexpr (MODE == MODE_REFRESH) put_state<D>(ax, states + ((grp - 1) * NACC + 1) * STATES, lane);
+    }
+    __syncthreads();
+    if (grp != 0 || !wk.wave_active) return;
+#pragma unroll
+    for (int k = 0; k < KS - 1; ++k) {
+        add_state<D>(acc, states + k * NACC * STATES, lane, p.c);
+        if constexpr (MODE == MODE_REFRESH) add_state<D>(ax, states + (k * NACC + 1) * STATES, lane, p.c);
+    }
+    if constexpr (MODE == MODE_REFRESH) {
+        store_split<D, 1>(p, acc, ax, head_off, qw0, L, r, g);
+    } else {
+        const float inv = 1.f / row_sum<D>(acc, 0, r);
+        const int qrow = qw0 + r;
+        if (qrow >= L) return;
+        const float* rl = (const float*)(smem + (iters & 1) * G::STAGE_ELEMS) + (qrow - q0) * D;
+#pragma unroll
+        for (int mb = 0; mb < G::NDB; ++mb) {
+#pragma clang fp contract(off)
+            const int col = 16 * mb + 4 * g;
+            if (col >= D) continue;
+            f32x4 out = acc.o[0][mb] * inv;
+            if constexpr (MODE == MODE_WINDOW) {
+                if (p.Rin) out = out + *(const f32x4*)(rl + col);
+            }
+            const u32x2 ov = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
+            for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + head_off + (size_t)qrow * D + col) = ov;
+        }
+    }
+}
+
 // Streaming copy of n16 16-byte units (AST output reuse).
 __global__ void __launch_bounds__(256) copy16_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n16) {
     const size_t stride = (size_t)gridDim.x * 256 * 4;
@@ -1023,6 +1214,28 @@ __global__ void __launch_bounds__(256) copy16_kernel(const u32x4* __restrict__ s
             if (i < n16) dst[i] = v[u];
         }
     }
+}
+
+// Key groups of a launch of 64-query workgroups (1: attn_kernel).  Two
+// workgroups of four wavefronts per CU are two wavefronts per SIMD; below that
+// the groups fill the SIMDs.  Combining them costs about 1 us, so a walk of
+// fewer than 8 tiles keeps one group (kernel times at 256 workgroups or fewer:
+// full attention of 4 tiles 6.8 us in one group, 7.9 in four; of 8 tiles 10.0
+// and 9.4; of 64 tiles 49.3 and 31.5; windows of 6 tiles 8.5 and 9.2, of 18
+// tiles 18.6 and 15.8; at 512 workgroups full attention of 16 tiles 19.8 us in
+// one, 18.9 in two).  A refresh, whose walk also carries two accumulators'
+// work, gains from 2 tiles on (4 tiles 10.6 -> 9.2 us, 64 tiles 57.9 -> 44.0);
+// its registers allow two groups and no more than 256 workgroups.
+template <int MODE>
+int key_groups(const AttnLaunch& a, long long nblocks) {
+    long long tiles = (a.L + BK - 1) / BK;
+    if (MODE == MODE_REFRESH) return nblocks <= 256 && tiles >= 2 ? 2 : 1;
+    if (MODE == MODE_WINDOW) {
+        const long long band = (2LL * a.w + 2 * BK - 2) / BK + 1;   // of 64 queries, at most
+        tiles = band < tiles ? band : tiles;
+    }
+    if (tiles < 8) return 1;
+    return nblocks <= 256 ? 4 : (nblocks <= 512 ? 2 : 1);
 }
 
 template <int D, int MODE, int QB>
@@ -1046,6 +1259,20 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
     p.c = (float)(1.4426950408889634 / __builtin_sqrt((double)D));
     static_assert((size_t)2 * G::STAGE_ELEMS * sizeof(uint16_t) * waves_per_simd<QB, MODE>() <= 160 * 1024,
                   "one workgroup per wave slot of a SIMD must fit in LDS");
+    if constexpr (QB == 1 && MODE != MODE_WINDOW_FINE && MODE != MODE_REFRESH_FINE) {
+        constexpr int KM = MODE == MODE_REFRESH_SPLIT ? MODE_REFRESH : MODE;
+        const int ks = key_groups<KM>(a, nb);
+        if constexpr (KM != MODE_REFRESH) {
+            if (ks == 4) {
+                hipLaunchKernelGGL((attn_keysplit_kernel<D, KM, 4>), dim3(p.nblocks), dim3(4 * NTHREADS), 0, stream, p);
+                return hipGetLastError();
+            }
+        }
+        if (ks == 2) {
+            hipLaunchKernelGGL((attn_keysplit_kernel<D, KM, 2>), dim3(p.nblocks), dim3(2 * NTHREADS), 0, stream, p);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((attn_kernel<D, MODE, QB>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
     return hipGetLastError();
 }
