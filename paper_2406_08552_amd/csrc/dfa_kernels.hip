@@ -65,13 +65,13 @@
 //   wavefront classifies the tile against its own queries (inside the band,
 //   outside, or straddling it with an element mask).
 //   The window kernel visits only the tiles that intersect the workgroup's
-//   band.  For L > 512 the refresh kernel runs ONE accumulator over two
+//   band.  For L > 1280 the refresh kernel runs ONE accumulator over two
 //   phases: first the in-band scores of the band tiles (after which the
 //   accumulator, normalised, is the window attention W; it is parked in the R
 //   buffer), then every out-of-band score, which turns the same accumulator
 //   into full attention.  R = O - W is formed in the epilogue.  Every score is
 //   used exactly once, only the few band-edge tiles are visited twice, and no
-//   second accumulator occupies registers.  Up to L = 512, where band-edge
+//   second accumulator occupies registers.  Up to L = 1280, where band-edge
 //   tiles are most of the walk, the refresh instead keeps two accumulators
 //   and visits every tile once (MODE_REFRESH_SPLIT).
 #include <hip/hip_runtime.h>
@@ -315,6 +315,17 @@ __device__ __forceinline__ void score_tile(const uint16_t* __restrict__ Ks, cons
     }
 }
 
+// Offsets [lo, lo + span] of a lane's in-band keys from its first, for query
+// qi: the band |qi - j| <= w cut to [0, L - 1]; a query beyond L whose band
+// holds no key gets an offset that no key has.
+__device__ __forceinline__ void band_range(int qi, int jbase, int L, int w, int& lo, uint32_t& span) {
+    const int a = (qi > w ? qi - w : 0) - jbase;
+    const uint32_t qpw = (uint32_t)qi + (uint32_t)w;    // < 2^32: qi < 2^31, w < 2^31
+    const int b = (int)(qpw < (uint32_t)(L - 1) ? qpw : (uint32_t)(L - 1)) - jbase;
+    lo = b < a ? (1 << 30) : a;
+    span = b < a ? 0u : (uint32_t)(b - a);
+}
+
 // Masks a score tile for one of the band or key masks (MASK_NONE: no-op).
 template <int MASK, int QB>
 __device__ __forceinline__ void mask_tile(Tile<QB>& S, int r, int g, int qrow0, int k0, int L, int w) {
@@ -333,12 +344,7 @@ __device__ __forceinline__ void mask_tile(Tile<QB>& S, int r, int g, int qrow0, 
             int lo = 0;
             uint32_t span = 0u;
             if constexpr (MASK == MASK_BAND_IN) {
-                const int qi = qrow0 + 16 * qb + r;
-                const int a = (qi > w ? qi - w : 0) - jbase;
-                const uint32_t qpw = (uint32_t)qi + (uint32_t)w;    // < 2^32: qi < 2^31, w < 2^31
-                const int b = (int)(qpw < (uint32_t)(L - 1) ? qpw : (uint32_t)(L - 1)) - jbase;
-                lo = b < a ? (1 << 30) : a;
-                span = b < a ? 0u : (uint32_t)(b - a);
+                band_range(qrow0 + 16 * qb + r, jbase, L, w, lo, span);
             }
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) {
@@ -356,6 +362,27 @@ __device__ __forceinline__ void mask_tile(Tile<QB>& S, int r, int g, int qrow0, 
                 }
             }
         }
+    }
+}
+
+// Splits a score tile by the band: S keeps the in-band scores, X gets the
+// others (of keys < L if S was masked so); -inf elsewhere.
+template <int QB>
+__device__ __forceinline__ void split_tile(Tile<QB>& S, Tile<QB>& X, int r, int g, int qrow0, int k0, int L, int w) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        int lo;
+        uint32_t span;
+        band_range(qrow0 + 16 * qb + r, k0 + 4 * g, L, w, lo, span);
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool in = (uint32_t)(16 * kb + i - lo) <= span;
+                const float s = S.s[qb][kb][i];
+                S.s[qb][kb][i] = in ? s : NEG_INF;
+                X.s[qb][kb][i] = in ? NEG_INF : s;
+            }
     }
 }
 
@@ -407,10 +434,20 @@ __device__ __forceinline__ void form_probs(const Acc<D, QB>& acc, const Tile<QB>
     }
 }
 
-// O^T += V^T P^T.  The A operand (16 dims x 32 keys) comes from the
-// row-major V tile through transposing reads: within each 16-lane row,
-// lane 4m+q addresses dims 16mb+4q..+3 of key k+m, and every lane receives
-// its own dim of keys k..k+3.
+// A operand of O^T += V^T P^T, dims 16 mb.. x keys 32 h.., from the row-major V
+// tile through transposing reads: within each 16-lane row, lane 4m+q addresses
+// dims 16mb+4q..+3 of key k+m, and every lane receives its own dim of keys
+// k..k+3.
+template <int D>
+__device__ __forceinline__ bf16x8 read_v(const uint16_t* Vs, int h, int mb, int r, int g) {
+    using G = Geo<D>;
+    const uint16_t* src = Vs + (32 * h + 4 * g + (r >> 2)) * G::VP + 16 * mb + 4 * (r & 3);
+    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
+    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src + 16 * G::VP));
+    return __builtin_bit_cast(bf16x8, s16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]});
+}
+
+// O^T += V^T P^T.
 template <int D, int QB, bool FINE>
 __device__ __forceinline__ void apply_probs(Acc<D, QB>& acc, const Probs<D, QB, FINE>& P, const uint16_t* Vs, int r,
                                             int g) {
@@ -419,21 +456,43 @@ __device__ __forceinline__ void apply_probs(Acc<D, QB>& acc, const Probs<D, QB, 
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) acc.l[qb] += P.psum[qb];
     }
-    const int tm = r >> 2, tq = r & 3;
 #pragma unroll
     for (int h = 0; h < BK / 32; ++h) {
 #pragma unroll
         for (int mb = 0; mb < G::NDB; ++mb) {
-            const uint16_t* src = Vs + (32 * h + 4 * g + tm) * G::VP + 16 * mb + 4 * tq;
-            const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
-            const s16x4 v1 =
-                __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src + 16 * G::VP));
-            const bf16x8 va = __builtin_bit_cast(bf16x8, s16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]});
+            const bf16x8 va = read_v<D>(Vs, h, mb, r, g);
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 acc.o[qb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, P.pb[qb][h], acc.o[qb][mb], 0, 0, 0);
                 if constexpr (FINE)
                     acc.o[qb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, P.pl[qb][h], acc.o[qb][mb], 0, 0, 0);
+            }
+        }
+    }
+}
+
+// The same for two accumulators with probabilities of their own, each V
+// fragment read once.
+template <int D, int QB>
+__device__ __forceinline__ void apply_probs2(Acc<D, QB>& acc, const Probs<D, QB, false>& P, Acc<D, QB>& ax,
+                                             const Probs<D, QB, false>& PX, const uint16_t* Vs, int r, int g) {
+    using G = Geo<D>;
+    if constexpr (!G::ONES) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            acc.l[qb] += P.psum[qb];
+            ax.l[qb] += PX.psum[qb];
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < BK / 32; ++h) {
+#pragma unroll
+        for (int mb = 0; mb < G::NDB; ++mb) {
+            const bf16x8 va = read_v<D>(Vs, h, mb, r, g);
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                acc.o[qb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, P.pb[qb][h], acc.o[qb][mb], 0, 0, 0);
+                ax.o[qb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, PX.pb[qb][h], ax.o[qb][mb], 0, 0, 0);
             }
         }
     }
@@ -686,8 +745,18 @@ struct Walk {
         Tile<QB> S;
         score_tile<D>(Ks, q, S, r, g);
         if (cls == TILE_BOUNDARY) {
-            accumulate<D, MASK_BAND_IN>(aw, S, Vs, r, g, qw0, k0, L, w, c);
-            accumulate<D, MASK_BAND_OUT>(ax, S, Vs, r, g, qw0, k0, L, w, c);
+            // One band test per score deals it to one of the two, and each V
+            // fragment is read once for both: against a mask and a PV pass of
+            // its own for each, 79.1 -> 75 us at (32, 16, 405, 72), 28.9 ->
+            // 24.1 us at (8, 16, 500, 64), where registers also fell from 154
+            // to 125 and a fourth wavefront per SIMD fits.
+            Tile<QB> X;
+            if (ragged) mask_tile<MASK_KEYS>(S, r, g, qw0, k0, L, w);
+            split_tile(S, X, r, g, qw0, k0, L, w);
+            Probs<D, QB, false> P, PX;
+            exact_probs<D, MASK_NONE>(aw, S, r, g, qw0, k0, L, w, c, P);
+            exact_probs<D, MASK_NONE>(ax, X, r, g, qw0, k0, L, w, c, PX);
+            apply_probs2(aw, P, ax, PX, Vs, r, g);
         } else if (cls == TILE_INSIDE) {
             if (ragged) accumulate<D, MASK_KEYS>(aw, S, Vs, r, g, qw0, k0, L, w, c);
             else accumulate<D, MASK_NONE>(aw, S, Vs, r, g, qw0, k0, L, w, c);
@@ -1020,14 +1089,16 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
 }
 
 // Three waves per SIMD with two query blocks per wavefront (register budget
-// 168), four with one (budget 128), three for the two-accumulator refresh: the
-// MFMA work of one wavefront overlaps the softmax arithmetic of the others.
-template <int QB, int KMODE>
-constexpr int waves_per_simd() { return QB == 1 && !split_refresh<KMODE>() ? 4 : 3; }
+// 168), four with one (budget 128): the MFMA work of one wavefront overlaps the
+// softmax arithmetic of the others.  The two-accumulator refresh fits four at
+// d = 64 (125 registers; 27.0 -> 23.9 us at (8, 16, 500, 64)); at d = 72 it
+// needs 143, and in 128 it spills (77.4 -> 82.1 us at (32, 16, 405, 72)).
+template <int D, int QB, int KMODE>
+constexpr int waves_per_simd() { return QB == 1 && (D == 64 || !split_refresh<KMODE>()) ? 4 : 3; }
 
 template <int D, int MODE, int QB>
 __global__ void __launch_bounds__(NTHREADS)
-    __attribute__((amdgpu_waves_per_eu(waves_per_simd<QB, MODE>(), waves_per_simd<QB, MODE>()))) attn_kernel(Params p) {
+    __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, QB, MODE>(), waves_per_simd<D, QB, MODE>()))) attn_kernel(Params p) {
     __shared__ __attribute__((aligned(16))) uint16_t smem[2 * Geo<D>::STAGE_ELEMS];
     attn_body<D, MODE, QB>(p, smem);
 }
@@ -1257,7 +1328,7 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
     if (nb <= 0 || nb > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     p.nblocks = (int)nb;
     p.c = (float)(1.4426950408889634 / __builtin_sqrt((double)D));
-    static_assert((size_t)2 * G::STAGE_ELEMS * sizeof(uint16_t) * waves_per_simd<QB, MODE>() <= 160 * 1024,
+    static_assert((size_t)2 * G::STAGE_ELEMS * sizeof(uint16_t) * waves_per_simd<D, QB, MODE>() <= 160 * 1024,
                   "one workgroup per wave slot of a SIMD must fit in LDS");
     if constexpr (QB == 1 && MODE != MODE_WINDOW_FINE && MODE != MODE_REFRESH_FINE) {
         constexpr int KM = MODE == MODE_REFRESH_SPLIT ? MODE_REFRESH : MODE;
@@ -1282,16 +1353,17 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
 // wavefronts hide latency there.  Long walks run faster with two blocks,
 // which halve the K/V tile copies per query.  The crossovers, measured at
 // d = 72 with interleaved timings: full attention up to L = 256 (4 key tiles),
-// refresh up to L = 1024, window attention up to a band of 1280 keys.  A band
-// that covers every key is full attention and takes full attention's choice,
-// so that the two give identical results.
+// window attention up to a band of 1280 keys.  A band that covers every key is
+// full attention and takes full attention's choice, so that the two give
+// identical results.  The refresh has one block up to L = 1280 in its split
+// form (launch_refresh) and two beyond.
 template <int MODE>
 bool one_query_block(const AttnLaunch& a) {
     // A launch whose 128-query workgroups would number at most one per CU
     // (one wavefront per SIMD) takes 64-query workgroups whatever its length:
     // measured 11% faster at (B, H, L) = (1, 16, 2048) and (4, 16, 512).
     if ((long long)a.B * a.H * ((a.L + bq<2>() - 1) / bq<2>()) <= 256) return true;
-    if constexpr (MODE == MODE_REFRESH) return a.L <= 1024;   // L <= 512 takes the split form
+    if constexpr (MODE == MODE_REFRESH) return false;
     if constexpr (MODE == MODE_WINDOW) {
         if (a.w < a.L - 1) return 2LL * a.w + 1 <= 1280;
     }
@@ -1314,9 +1386,12 @@ bool head_dim_supported(int d) { return d == 64 || d == 72; }
 
 hipError_t launch_full(const AttnLaunch& a, hipStream_t s) { return launch_mode<MODE_FULL>(a, s); }
 hipError_t launch_asc(const AttnLaunch& a, hipStream_t s) { return launch_mode<MODE_ASC>(a, s); }
-// Refresh: the one-pass two-accumulator form up to L = 512 (8 key tiles, where
-// band-edge tiles are most of the walk), the two-phase form beyond (measured:
-// L = 256 -16%, 405 -6%, 1024 +3% for the one-pass form).
+// Refresh: the one-pass two-accumulator form up to L = 1280 (20 key tiles),
+// where band-edge tiles, which the two-phase form visits twice, are a large
+// part of the walk, the two-phase form beyond.  Measured one-pass against
+// two-phase, us: (8, 16, 1024, 72) 79.2 and 86.0, (16, 16, 700, 64) 75.5 and
+// 92.6, (16, 4, 1300, 64) 61.6 and 64.5, (8, 16, 1500, 72) 161.5 and 150.4,
+// (4, 16, 2048, 64) 117.4 and 109.0.
 // Bands of at most 31 keys take the two-phase form with split probabilities
 // in its in-band phase (64-query workgroups), so that W, and with it R and
 // every reuse that adds R, carries no unaveraged bf16 rounding of its weights.
@@ -1328,7 +1403,7 @@ hipError_t launch_refresh(const AttnLaunch& a, hipStream_t s) {
             default: return hipErrorInvalidValue;
         }
     }
-    if (a.L > 512) return launch_mode<MODE_REFRESH>(a, s);
+    if (a.L > 1280) return launch_mode<MODE_REFRESH>(a, s);
     switch (a.d) {
         case 64: return launch_attn<64, MODE_REFRESH_SPLIT, 1>(a, s);
         case 72: return launch_attn<72, MODE_REFRESH_SPLIT, 1>(a, s);

@@ -1,7 +1,7 @@
 """GPU parity of the launches that deal a workgroup's key tiles to several
 wavefront groups (at most 512 workgroups of 64 queries and walks of at least 8
 tiles; refreshes of at most 256 workgroups), at the edges of that rule, against
-float64 attention on the same bf16 inputs.  Bars: those of the attention
+float64 attention on the same bf16 inputs, and of the refresh forms beside it.  Bars: those of the attention
 parity tests (max 1e-2, mean 1e-3 for unit-variance V; the fp32 residual R
 carries the same probability rounding)."""
 import pytest
@@ -40,6 +40,11 @@ def _check(name, got, ref):
     (1, 2, 3000, 72, 200),      # windows of which some groups see nothing
     (1, 4, 70, 72, 20),         # a refresh of two tiles
     (3, 5, 65, 64, 16),         # the second tile of one key
+    # more than 256 workgroups, one group: the refresh's one-pass form and its last length
+    (2, 16, 577, 72, 72),
+    (2, 7, 1280, 64, 160),
+    (1, 14, 1280, 72, 700),
+    (2, 7, 1281, 72, 160),      # two phases
 ])
 @pytest.mark.parametrize("spread", [1.0, 3.0])
 def test_keysplit_vs_fp64(B, H, L, d, w, spread):
