@@ -4,7 +4,10 @@ Argument marshalling only: each function takes torch tensors, checks that they
 are contiguous [B, H, L, d] tensors on a GPU (bf16, the residual R fp32),
 reads B, H, L, d from the
 shapes, and calls the C function of the same name with the tensors' device
-pointers and the current HIP stream.  All computation happens in the
+pointers and the current HIP stream.  Ordinary calls on the current stream are
+marshalled by the native ``_dfa_binding`` (csrc/dfa_binding.cpp: 6.5 to 7 us of
+Python and ctypes work a call otherwise); it declines anything else (-1), and
+the Python code below then checks, raises or calls.  All computation happens in the
 library's HIP kernels; there is no fallback of any kind.  A non-OK status
 raises :class:`DfaError` with the library's message.
 
@@ -18,7 +21,7 @@ import os
 
 import numpy as np
 
-from .build import LIB_PATH
+from .build import BINDING_PATH, LIB_PATH
 
 DFA_OK, DFA_ERR_INVALID_ARG, DFA_ERR_UNSUPPORTED, DFA_ERR_HIP = 0, 1, 2, 3
 FULL, WARS_REFRESH, WARS_REUSE, AST_REUSE, ASC_REUSE = 0, 1, 2, 3, 4
@@ -87,6 +90,37 @@ def lib() -> ctypes.CDLL:
     return _LIB
 
 
+_NATIVE = None
+
+
+def _native():
+    """The native marshalling, bound to this process's library; raises if it
+    is missing."""
+    global _NATIVE
+    if _NATIVE is None:
+        import importlib.util
+        torch, L = _torch(), lib()   # torch first: the extension's symbols come from it
+        if not os.path.exists(BINDING_PATH):
+            raise RuntimeError(f"{BINDING_PATH} is missing: build it first "
+                               "(python -c 'import __graft_entry__ as g; g.build()')")
+        spec = importlib.util.spec_from_file_location("_dfa_binding", BINDING_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        names = ("dfa_attn_full", "dfa_attn_full_and_residual", "dfa_attn_window_plus_residual", "dfa_plan_step",
+                 "dfa_qkv_proj", "dfa_out_proj", "dfa_module_step", "dfa_mrae")
+        mod.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+                 *[ctypes.cast(getattr(L, n), _vp).value for n in names])
+        _NATIVE = mod
+    return _NATIVE
+
+
+def _done(status: int) -> bool:
+    """Whether a natively marshalled call was made (raises if it failed)."""
+    if status > 0:
+        _check(status)
+    return status == 0
+
+
 def last_error() -> str:
     return lib().dfa_last_error().decode()
 
@@ -148,12 +182,16 @@ def _stream(stream) -> int:
 
 def dfa_attn_full(Q, K, V, O, w: int = 0, stream=None) -> None:
     """O = softmax(Q K^T / sqrt(d)) V."""
+    if stream is None and _done(_native().attn(0, Q, K, V, O, None, w)):
+        return
     B, H, L, d = _shape(Q, K, V, O)
     _check(lib().dfa_attn_full(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), None, B, H, L, d, w, _stream(stream)))
 
 
 def dfa_attn_full_and_residual(Q, K, V, O, R, w: int, stream=None) -> None:
     """O = full attention and R (fp32) = O - window attention (|i-j| <= w)."""
+    if stream is None and _done(_native().attn(1, Q, K, V, O, R, w)):
+        return
     B, H, L, d = _shape(Q, K, V, O, R=R)
     _check(lib().dfa_attn_full_and_residual(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(R), B, H, L, d, w,
                                             _stream(stream)))
@@ -161,6 +199,8 @@ def dfa_attn_full_and_residual(Q, K, V, O, R, w: int, stream=None) -> None:
 
 def dfa_attn_window_plus_residual(Q, K, V, O, R, w: int, stream=None) -> None:
     """O = window attention (|i-j| <= w) + R (fp32; None: window attention only)."""
+    if stream is None and _done(_native().attn(2, Q, K, V, O, R, w)):
+        return
     B, H, L, d = _shape(Q, K, V, O, R=R)
     _check(lib().dfa_attn_window_plus_residual(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(R), B, H, L, d, w,
                                                _stream(stream)))
@@ -168,6 +208,8 @@ def dfa_attn_window_plus_residual(Q, K, V, O, R, w: int, stream=None) -> None:
 
 def dfa_plan_step(code: int, Q, K, V, O, R, Ocache, w: int, stream=None) -> None:
     """One plan entry of one layer (see include/dfa.h for the cache rules)."""
+    if stream is None and _done(_native().plan_step(code, Q, K, V, O, R, Ocache, w)):
+        return
     B, H, L, d = _shape(O, Q, K, V, Ocache, R=R)
     _check(lib().dfa_plan_step(int(code), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(R), _ptr(Ocache),
                                B, H, L, d, w, _stream(stream)))
@@ -199,6 +241,8 @@ def _weights(Wqkv, bqkv, Wo, bo, C):
 
 def dfa_qkv_proj(X, Wqkv, bqkv, Q, K, V, stream=None) -> None:
     """Q, K, V = split(X Wqkv^T + bqkv); X [B, L, H*d] bf16, Q/K/V [B, H, L, d] bf16."""
+    if stream is None and _done(_native().qkv_proj(X, Wqkv, bqkv, Q, K, V)):
+        return
     import torch
     B, H, L, d = _shape(Q, K, V)
     _proj_shapes(X, Q)
@@ -209,6 +253,8 @@ def dfa_qkv_proj(X, Wqkv, bqkv, Q, K, V, stream=None) -> None:
 
 def dfa_out_proj(O, Wo, bo, Y, stream=None) -> None:
     """Y = merge(O) Wo^T + bo; O [B, H, L, d] bf16, Y [B, L, H*d] bf16."""
+    if stream is None and _done(_native().out_proj(O, Wo, bo, Y)):
+        return
     import torch
     B, H, L, d = _shape(O)
     _proj_shapes(Y, O)
@@ -222,6 +268,8 @@ def dfa_module_step(code: int, X, Wqkv, bqkv, Wo, bo, Q, K, V, O, R, Y, Ycache, 
     """One attention module with H heads under a plan code (see include/dfa.h).
     Shapes come from Y [B, L, C] (d = C / H); for AST every other tensor may
     be None."""
+    if stream is None and _done(_native().module_step(code, X, Wqkv, bqkv, Wo, bo, Q, K, V, O, R, Y, Ycache, w, H)):
+        return
     import torch
     if Y is None or Y.dim() != 3:
         raise ValueError("Y must be a [B, L, C] tensor")
@@ -252,6 +300,8 @@ def _nbytes(t) -> int:
 def dfa_mrae(A, B, workspace, result, stream=None) -> None:
     """result (a 1-element fp64 GPU tensor) = MRAE of two bf16 tensors of the
     same size; workspace: a GPU tensor of at least MRAE_WORKSPACE_BYTES bytes."""
+    if stream is None and _done(_native().mrae(A, B, workspace, result)):
+        return
     import torch
     if A.dtype != torch.bfloat16 or B.dtype != torch.bfloat16 or A.numel() != B.numel():
         raise ValueError("A and B must be bf16 tensors of the same size")
