@@ -420,6 +420,7 @@ dfa_status dfa_module_step(int code, const void* X, const void* Wqkv, const void
     if ((st = hip_status(dfa::launch_qkv_proj(pq, stream), "QKV projection launch")) != DFA_OK) return st;
 
     dfa::AttnLaunch a = make_launch(Q, K, V, s);
+    a.read_next = true;   // by the output projection
     a.B = Bc;
     a.dst[0] = O;
     a.ndst = 1;

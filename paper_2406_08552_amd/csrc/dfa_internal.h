@@ -19,6 +19,7 @@ struct AttnLaunch {
     void* dst[4];
     int ndst;
     int B, H, L, d, w;
+    bool read_next;    // the next launch reads the outputs: they are stored with allocation in L2
 };
 
 // One projection launch of the attention module over B * L tokens.

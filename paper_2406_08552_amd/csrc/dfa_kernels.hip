@@ -170,6 +170,7 @@ struct Params {
     int n_qt;                 // query tiles per (batch, head)
     int nblocks;
     float c;                  // log2(e) / sqrt(d)
+    int read_next;            // store O with allocation in L2
 };
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -834,17 +835,96 @@ struct Walk {
 template <int KMODE>
 constexpr bool split_refresh() { return KMODE == MODE_REFRESH_SPLIT; }
 
+// Orders a wavefront's LDS accesses before and after it (its lanes hand values
+// to each other; a wavefront's LDS accesses complete in order).
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Pitch, in elements, of 16 output rows on their way through LDS: rows of bf16
+// and of fp32 spread over the banks for both head dims.
+constexpr int OUT_PITCH = 72;
+constexpr int OUT_ELEMS = 16 * OUT_PITCH;   // bf16 elements of a wavefront's rows; fp32 rows take twice that
+
+// Stores the 16 rows of a query block to every destination, the first `rows`
+// of them, from row offset `at`.  A lane holds 4 dims of one query, so stores
+// straight from it write 32-byte (bf16) or 64-byte (fp32) pieces of 16 rows;
+// passed through LDS `Wl` (the wavefront's own), they leave as whole lines in
+// row order, without allocation in L2 (nothing in the launch reads them again;
+// in a module step the next launch does, and there they are allocated: 163
+// against 167 us at (8, 16, 1024, 72)).
+// Direct, in row order, and in row order without allocation, us: full
+// (32, 16, 405, 72) 49.0, 49.7, 46.4; refresh (8, 16, 1024, 72) 78.8, 79.3,
+// 74.2, (16, 16, 700, 64) 74.1, 73.0, 66.9; reuse (2, 16, 4096, 72) 68.5, 67.4,
+// 64.7, (8, 16, 1024, 72) 33.6, 33.3, 30.5.  Direct without allocation, pieces
+// of lines, is slower than all three (55.3, 86.7, 74.8, 72.9, 40.9).
+template <int D>
+__device__ __forceinline__ void store_rows(const Params& p, const u32x2 (&o)[Geo<D>::NDB], uint16_t* Wl, size_t at, int rows,
+                                           int lane) {
+    using G = Geo<D>;
+    const int r = lane & 15, g = lane >> 4;
+    lds_fence();
+#pragma unroll
+    for (int mb = 0; mb < G::NDB; ++mb)
+        if (16 * mb + 4 * g < D) *(u32x2*)(Wl + r * OUT_PITCH + 16 * mb + 4 * g) = o[mb];
+    lds_fence();
+    constexpr int NIT = (16 * G::NCH + 63) / 64;
+    u32x4 v[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int idx = it * 64 + lane, row = idx / G::NCH, ch = idx - row * G::NCH;
+        v[it] = u32x4{0u, 0u, 0u, 0u};
+        if (idx < 16 * G::NCH) v[it] = *(const u32x4*)(Wl + row * OUT_PITCH + 8 * ch);
+    }
+    for (int di = 0; di < p.ndst; ++di) {
+        u32x4* out = (u32x4*)(p.dst[di] + at);
+#pragma unroll
+        for (int it = 0; it < NIT; ++it)
+            if (it * 64 + lane < rows * G::NCH) {
+                if (p.read_next) {
+                    asm volatile("" ::: "memory");   // on both sides: else the two forms are merged into the plain one
+                    out[it * 64 + lane] = v[it];
+                    asm volatile("" ::: "memory");
+                } else {
+                    __builtin_nontemporal_store(v[it], out + it * 64 + lane);
+                }
+            }
+    }
+}
+
+// The same for the residual, fp32.
+template <int D>
+__device__ __forceinline__ void store_residual(const Params& p, const f32x4 (&o)[Geo<D>::NDB], uint16_t* Wl, size_t at,
+                                               int rows, int lane) {
+    using G = Geo<D>;
+    const int r = lane & 15, g = lane >> 4;
+    float* Wf = (float*)Wl;
+    lds_fence();
+#pragma unroll
+    for (int mb = 0; mb < G::NDB; ++mb)
+        if (16 * mb + 4 * g < D) *(f32x4*)(Wf + r * OUT_PITCH + 16 * mb + 4 * g) = o[mb];
+    lds_fence();
+    constexpr int N4 = D / 4;
+#pragma unroll
+    for (int it = 0; it < (16 * N4 + 63) / 64; ++it) {
+        const int idx = it * 64 + lane, row = idx / N4, c4 = idx - row * N4;
+        if (idx < rows * N4) __builtin_nontemporal_store(*(const f32x4*)(Wf + row * OUT_PITCH + 4 * c4), (f32x4*)(p.Rout + at) + idx);
+    }
+}
+
 // Epilogue of a two-accumulator refresh: W = aw / lw, O from both, each scaled
 // from its own running max to the larger one, R = O - W.
 template <int D, int QB>
 __device__ __forceinline__ void store_split(const Params& p, const Acc<D, QB>& aw, const Acc<D, QB>& ax, size_t head_off,
-                                            int qw0, int L, int r, int g) {
+                                            int qw0, int L, uint16_t* Wl, int lane) {
     using G = Geo<D>;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const int qrow = qw0 + 16 * qb + r;
+        const int q0 = qw0 + 16 * qb;
         // row sums first: they exchange values across lanes
-        const float lw = row_sum<D>(aw, qb, r), lx = row_sum<D>(ax, qb, r);
+        const float lw = row_sum<D>(aw, qb, lane & 15), lx = row_sum<D>(ax, qb, lane & 15);
         const bool has_x = ax.thr[qb] != NEG_INF;
         const float mw = aw.running_max(qb);
         const float mx = ax.running_max(qb);
@@ -853,20 +933,20 @@ __device__ __forceinline__ void store_split(const Params& p, const Acc<D, QB>& a
         const float sx = has_x ? __builtin_amdgcn_exp2f(mx - mm) : 0.f;
         const float invw = 1.f / lw;
         const float inv = 1.f / (lw * sw + lx * sx);
-        if (qrow >= L) continue;
-        const size_t row_off = head_off + (size_t)qrow * D;
+        const size_t at = head_off + (size_t)q0 * D;
+        const int rows = min(16, L - q0);
+        f32x4 res[G::NDB];
+        u32x2 ob[G::NDB];
 #pragma unroll
         for (int mb = 0; mb < G::NDB; ++mb) {
 #pragma clang fp contract(off)
-            const int col = 16 * mb + 4 * g;
-            if (col >= D) continue;
-            const size_t off = row_off + col;
             const f32x4 wv = aw.o[qb][mb] * invw;
             const f32x4 o = has_x ? (aw.o[qb][mb] * sw + ax.o[qb][mb] * sx) * inv : wv;
-            *(f32x4*)(p.Rout + off) = o - wv;
-            const u32x2 ov = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
-            for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + off) = ov;
+            res[mb] = o - wv;
+            ob[mb] = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
         }
+        store_residual<D>(p, res, Wl, at, rows, lane);
+        store_rows<D>(p, ob, Wl, at, rows, lane);
     }
 }
 
@@ -885,7 +965,7 @@ __device__ __forceinline__ void refresh_split(const Params& p, uint16_t* smem, W
     wait_vm_all();
     __syncthreads();
     wk.run_split(aw, ax, q, 0, ntiles);
-    if (wk.wave_active) store_split<D, QB>(p, aw, ax, head_off, wk.qw0, wk.L, wk.r, wk.g);
+    if (wk.wave_active) store_split<D, QB>(p, aw, ax, head_off, wk.qw0, wk.L, smem + (wk.tid >> 6) * 2 * OUT_ELEMS, wk.tid & 63);
 }
 
 template <int D, int KMODE, int QB>
@@ -930,8 +1010,22 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
         }
     }
 
+    // Q fragments, zero beyond L and beyond d (in line: called, the window walk of
+    // 512 workgroups at (8, 16, 256, 72) measured 9.06 us, in line 9.01)
     QFrag<D, QB> q;
-    load_q<D, QB>(q, Qbh, qw0, L, r, g);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int qrow = qw0 + 16 * qb + r;
+        const bool ok = qrow < L;
+        const uint16_t* qp = Qbh + (size_t)(ok ? qrow : 0) * D;
+#pragma unroll
+        for (int c = 0; c < G::NC32; ++c)
+            q.a[qb][c] = as_bf16x8(ok ? *(const u32x4*)(qp + 32 * c + 8 * g) : u32x4{0u, 0u, 0u, 0u});
+        q.t[qb] = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
+        if constexpr (G::TAIL > 0) {
+            if (ok && 8 * g < G::TAIL) q.t[qb] = as_bf16x8(*(const u32x4*)(qp + G::D32 + 8 * g));
+        }
+    }
 
     // the fast update measured 1-2% faster in the long walks of two query
     // blocks per wavefront and about 1% slower in the short walks of one
@@ -1050,19 +1144,34 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
 
     if (!wk.wave_active) return;
 
-    // epilogue: normalise, form R, store bf16 to every destination
+    // epilogue: normalise, form R, store bf16 to every destination.  The rows
+    // pass through the stage that holds no residual rows (both stages are free
+    // after the walk's last barrier), except in the two-phase refresh with two
+    // query blocks: at d = 72 it has no registers left for it (nine spills; 148 ->
+    // 152 us at (8, 16, 1500, 72)), at d = 64 it gained less than 1%.
+    constexpr bool DIRECT = MODE == MODE_REFRESH && QB == 2;
+    static_assert(NWAVES * OUT_ELEMS <= G::STAGE_ELEMS && NWAVES * 2 * OUT_ELEMS <= 2 * G::STAGE_ELEMS, "output rows must fit");
+    uint16_t* Wl = MODE == MODE_REFRESH ? smem + wave * 2 * OUT_ELEMS
+                                        : smem + (wk.stage ^ 1) * G::STAGE_ELEMS + wave * OUT_ELEMS;
+    int el = tid;   // opaque: nothing of the epilogue's addressing is formed before the walk
+    asm volatile("" : "+v"(el));
+    el &= 63;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const int qrow = qw0 + 16 * qb + r;
         const float inv = 1.f / row_sum<D>(acc, qb, r);
-        if (qrow >= L) continue;
         const size_t row_off = head_off + (size_t)qrow * D;
+        f32x4 res[G::NDB];
+        u32x2 ob[G::NDB];
 #pragma unroll
         for (int mb = 0; mb < G::NDB; ++mb) {
             // no fma contraction: o must be rounded exactly as the parked W was
 #pragma clang fp contract(off)
             const int col = 16 * mb + 4 * g;
-            if (col >= D) continue;
+            const bool ok = qrow < L && col < D;
+            if constexpr (DIRECT) {
+                if (!ok) continue;
+            }
             const size_t off = row_off + col;
             const f32x4 o = acc.o[qb][mb] * inv;
             f32x4 out = o;
@@ -1070,20 +1179,29 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
                 // R is the exact difference of the two rounded fp32 results (a
                 // band covering every key gives R == 0 exactly); the window
                 // result parked above is read back by the lane that wrote it.
-                const f32x4 win = *(const f32x4*)(p.Rout + off);
-                *(f32x4*)(p.Rout + off) = o - win;
+                res[mb] = o;
+                if (DIRECT || ok) res[mb] = o - *(const f32x4*)(p.Rout + off);
             }
             if constexpr (MODE == MODE_WINDOW) {
                 if (wk.rpre) {
                     // the walk's last iteration left the rows in the stage it freed
                     const float* rl = (const float*)(smem + wk.stage * G::STAGE_ELEMS);
-                    out = o + *(const f32x4*)(rl + (qrow - q0) * D + col);
+                    if (ok) out = o + *(const f32x4*)(rl + (qrow - q0) * D + col);
                 } else if (p.Rin) {
-                    out = o + *(const f32x4*)(p.Rin + off);
+                    if (ok) out = o + *(const f32x4*)(p.Rin + off);
                 }
             }
-            const u32x2 ov = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
-            for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + off) = ov;
+            ob[mb] = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
+            if constexpr (DIRECT) {
+                *(f32x4*)(p.Rout + off) = res[mb];
+                for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + off) = ob[mb];
+            }
+        }
+        if constexpr (!DIRECT) {
+            const size_t at = head_off + (size_t)(qw0 + 16 * qb) * D;
+            const int rows = min(16, L - (qw0 + 16 * qb));
+            if constexpr (MODE == MODE_REFRESH) store_residual<D>(p, res, Wl, at, rows, el);
+            store_rows<D>(p, ob, Wl, at, rows, el);
         }
     }
 }
@@ -1156,7 +1274,9 @@ attn_keysplit_kernel(Params p) {
     // residual rows), or from the start for a refresh's two accumulators
     constexpr int NACC = MODE == MODE_REFRESH ? 2 : 1, STATE0 = MODE == MODE_REFRESH ? 0 : 2 * G::STAGE_ELEMS;
     constexpr int STATES = NWAVES * state_elems<D>();
-    static_assert(STATE0 + (KS - 1) * NACC * STATES <= KS * 2 * G::STAGE_ELEMS, "the states must fit the stages");
+    // a refresh's outputs leave through LDS behind the states
+    constexpr int OUT = MODE == MODE_REFRESH ? NWAVES * 2 * OUT_ELEMS : 0;
+    static_assert(STATE0 + (KS - 1) * NACC * STATES + OUT <= KS * 2 * G::STAGE_ELEMS, "the states must fit the stages");
     static_assert(bq<1>() * D * 4 <= G::STAGE_ELEMS * 2, "residual rows must fit one LDS stage");
     const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NTHREADS);
     const int tid = threadIdx.x % NTHREADS;
@@ -1248,24 +1368,23 @@ attn_keysplit_kernel(Params p) {
         if constexpr (MODE == MODE_REFRESH) add_state<D>(ax, states + (k * NACC + 1) * STATES, lane, p.c);
     }
     if constexpr (MODE == MODE_REFRESH) {
-        store_split<D, 1>(p, acc, ax, head_off, qw0, L, r, g);
+        store_split<D, 1>(p, acc, ax, head_off, qw0, L, smem + STATE0 + (KS - 1) * NACC * STATES + wave * 2 * OUT_ELEMS, lane);
     } else {
         const float inv = 1.f / row_sum<D>(acc, 0, r);
-        const int qrow = qw0 + r;
-        if (qrow >= L) return;
-        const float* rl = (const float*)(smem + (iters & 1) * G::STAGE_ELEMS) + (qrow - q0) * D;
+        const float* rl = (const float*)(smem + (iters & 1) * G::STAGE_ELEMS) + (wave * 16 + r) * D;
+        u32x2 ob[G::NDB];
 #pragma unroll
         for (int mb = 0; mb < G::NDB; ++mb) {
 #pragma clang fp contract(off)
             const int col = 16 * mb + 4 * g;
-            if (col >= D) continue;
             f32x4 out = acc.o[0][mb] * inv;
             if constexpr (MODE == MODE_WINDOW) {
-                if (p.Rin) out = out + *(const f32x4*)(rl + col);
+                if (p.Rin && qw0 + r < L && col < D) out = out + *(const f32x4*)(rl + col);
             }
-            const u32x2 ov = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
-            for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + head_off + (size_t)qrow * D + col) = ov;
+            ob[mb] = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
         }
+        // through the stage of group 0 that holds no residual rows
+        store_rows<D>(p, ob, smem + (~iters & 1) * G::STAGE_ELEMS + wave * OUT_ELEMS, head_off + (size_t)qw0 * D, min(16, L - qw0), lane);
     }
 }
 
@@ -1319,6 +1438,7 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
     p.Rin = (const float*)a.Rin;
     p.Rout = (float*)a.Rout;
     p.ndst = a.ndst;
+    p.read_next = a.read_next;
     for (int i = 0; i < 4; ++i) p.dst[i] = (uint16_t*)(i < a.ndst ? a.dst[i] : nullptr);
     p.H = a.H;
     p.L = a.L;

@@ -23,6 +23,17 @@
 // the 32-key PV chunk at or beyond L have zero probability and zero V rows.
 // For d = 72 the LDS column 72 of V holds 1.0, so the PV product also yields
 // the softmax row sum of the same bf16 probabilities that weight V.
+//
+// HBM bandwidth bounds these kernels, and the shape of their stores decided
+// how much of it they reached.  The MFMA layout leaves a lane 4 dims of one
+// query, so a store straight from it writes 32-byte pieces of 16 rows.  The
+// outputs (and a refresh's R at d = 72, whose 288-byte rows straddle lines)
+// instead pass through the wavefront's LDS rows, which V has left, and leave
+// as whole lines in row order, without allocation in L2 (nothing here reads
+// them again; in a module step the next launch does, and O is allocated).  Direct, in row order, and in row order without allocation, at
+// 12960 sequences of (16, 72): full 28.1, 24.7, 20.6 us; window with R 39.8,
+// 35.8, 33.7 us; refresh 43.9, 40.2, 31.1 us.  Stores without allocation of
+// pieces of a line are the slowest of all (L = 32 refresh 13.1 -> 19.8 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -58,6 +69,10 @@ struct SGeo {
     static constexpr int VP = NDB * 16 + 8;         // LDS row pitch of V (elements)
     static constexpr int VCH = VP / 8;              // 16-byte chunks per LDS row
     static_assert(VP % 8 == 0 && VCH > NCH, "V pitch");
+    // LDS row pitch of an output on its way out: rows 144 bytes apart spread
+    // over the banks (128 would not)
+    static constexpr int OP = 72;
+    static_assert(OP % 8 == 0 && OP >= D && OP <= VP, "output pitch");
 };
 
 struct SParams {
@@ -68,6 +83,7 @@ struct SParams {
     float* Rout;              // MODE_REFRESH: fp32 residual output
     uint16_t* dst[4];         // every destination receives the same output
     int ndst;
+    int read_next;            // store O with allocation in L2
     int nseq;                 // B * H sequences of L tokens
     int L, w;
     float c;                  // log2(e) / sqrt(d)
@@ -86,6 +102,14 @@ __device__ __forceinline__ float pair_acc(uint32_t w, float acc) {
 }
 
 __device__ __forceinline__ u32x4 load16(const uint16_t* p) { return *(const u32x4*)p; }
+
+// Orders this wavefront's LDS accesses before and after it (its lanes hand
+// values to each other; a wavefront's LDS accesses complete in order).
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // The rounding residuals lo - bf16(lo) and hi - bf16(hi) of a pair packed by
 // pack_bf16x2 (exact in fp32), themselves packed to bf16.
@@ -152,7 +176,11 @@ short_attn_kernel(SParams p) {
     using G = SGeo<D>;
     constexpr int MODE = KMODE == MODE_ASC ? MODE_FULL : KMODE;
     constexpr int ROWS = 16 * NB;
-    __shared__ __attribute__((aligned(16))) uint16_t smem[SW * ROWS * G::VP];
+    // a refresh at d = 72 sends R through LDS as well, as fp32 rows
+    constexpr bool R_ROWS = MODE == MODE_REFRESH && D == 72;
+    constexpr int WELEMS = ROWS * (R_ROWS ? 2 * D : G::VP);   // a wavefront's share
+    static_assert(WELEMS >= ROWS * G::VP, "V must fit");
+    __shared__ __attribute__((aligned(16))) uint16_t smem[SW * WELEMS];
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -165,7 +193,7 @@ short_attn_kernel(SParams p) {
     const uint16_t* __restrict__ Qs = p.Q + off;
     const uint16_t* __restrict__ Ks = p.K + off;
     const uint16_t* __restrict__ Vs = p.V + off;
-    uint16_t* Vl = smem + wave * ROWS * G::VP;
+    uint16_t* Vl = smem + wave * WELEMS;
 
     // V rows into this wavefront's LDS rows: rows at or beyond L are zero,
     // chunk NCH is (1, 0, ..., 0) for d = 72 (row-sum column), later chunks
@@ -261,6 +289,7 @@ short_attn_kernel(SParams p) {
         }
     }
 
+    u32x2 ob[NB][G::NDB];   // the output, packed
 #pragma unroll
     for (int qb = 0; qb < NB; ++qb) {
         const int qi = 16 * qb + r;
@@ -292,24 +321,63 @@ short_attn_kernel(SParams p) {
             }
             inv[set] = 1.f / l;
         }
-        if (qi >= L) continue;
-        const size_t row_off = off + (size_t)qi * D;
 #pragma unroll
         for (int mb = 0; mb < G::NDB; ++mb) {
             // no fma contraction: R must be the difference of the two rounded results
 #pragma clang fp contract(off)
             const int col = 16 * mb + 4 * g;
-            if (col >= D) continue;
-            const size_t at = row_off + col;
             const f32x4 ov = o[0][mb] * inv[0];
             f32x4 out = ov;
-            if constexpr (MODE == MODE_REFRESH) *(f32x4*)(p.Rout + at) = ov - o[NSET - 1][mb] * inv[NSET - 1];
+            if constexpr (MODE == MODE_REFRESH) {
+                const f32x4 res = ov - o[NSET - 1][mb] * inv[NSET - 1];
+                if (qi < L && col < D) {
+                    if constexpr (R_ROWS) *(f32x4*)((float*)Vl + qi * D + col) = res;
+                    else __builtin_nontemporal_store(res, (f32x4*)(p.Rout + off + (size_t)qi * D + col));
+                }
+            }
             if constexpr (MODE == MODE_WINDOW) {
                 if (p.Rin) out = ov + rin[qb][mb];
             }
-            const u32x2 st = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
-            for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + at) = st;
+            ob[qb][mb] = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
         }
+    }
+
+    if constexpr (R_ROWS) {
+        lds_fence();
+#pragma unroll
+        for (int it = 0; it < (ROWS * D / 4 + 63) / 64; ++it) {
+            const int c4 = it * 64 + lane;
+            if (c4 < L * (D / 4)) __builtin_nontemporal_store(*(const f32x4*)((const float*)Vl + c4 * 4), (f32x4*)(p.Rout + off) + c4);
+        }
+        lds_fence();
+    }
+#pragma unroll
+    for (int qb = 0; qb < NB; ++qb)
+#pragma unroll
+        for (int mb = 0; mb < G::NDB; ++mb)
+            if (16 * mb + 4 * g < D) *(u32x2*)(Vl + (16 * qb + r) * G::OP + 16 * mb + 4 * g) = ob[qb][mb];
+    lds_fence();
+    constexpr int OIT = (ROWS * G::NCH + 63) / 64;
+    u32x4 ov[OIT];
+#pragma unroll
+    for (int it = 0; it < OIT; ++it) {
+        const int idx = it * 64 + lane, row = idx / G::NCH, ch = idx - row * G::NCH;
+        ov[it] = u32x4{0u, 0u, 0u, 0u};
+        if (idx < L * G::NCH) ov[it] = *(const u32x4*)(Vl + row * G::OP + 8 * ch);
+    }
+    for (int di = 0; di < p.ndst; ++di) {
+        u32x4* out = (u32x4*)(p.dst[di] + off);
+#pragma unroll
+        for (int it = 0; it < OIT; ++it)
+            if (it * 64 + lane < L * G::NCH) {
+                if (p.read_next) {
+                    asm volatile("" ::: "memory");   // on both sides: else the two forms are merged into the plain one
+                    out[it * 64 + lane] = ov[it];
+                    asm volatile("" ::: "memory");
+                } else {
+                    __builtin_nontemporal_store(ov[it], out + it * 64 + lane);
+                }
+            }
     }
 }
 
@@ -322,6 +390,7 @@ hipError_t launch_short_attn(const AttnLaunch& a, hipStream_t stream) {
     p.Rin = (const float*)a.Rin;
     p.Rout = (float*)a.Rout;
     p.ndst = a.ndst;
+    p.read_next = a.read_next;
     for (int i = 0; i < 4; ++i) p.dst[i] = (uint16_t*)(i < a.ndst ? a.dst[i] : nullptr);
     const long long nseq = (long long)a.B * a.H;
     const long long nblocks = (nseq + SW - 1) / SW;
