@@ -853,8 +853,8 @@ constexpr int OUT_ELEMS = 16 * OUT_PITCH;   // bf16 elements of a wavefront's ro
 // straight from it write 32-byte (bf16) or 64-byte (fp32) pieces of 16 rows;
 // passed through LDS `Wl` (the wavefront's own), they leave as whole lines in
 // row order, without allocation in L2 (nothing in the launch reads them again;
-// in a module step the next launch does, and there they are allocated: 163
-// against 167 us at (8, 16, 1024, 72)).
+// in a module step the next launch does, and there they are allocated, which
+// takes 2% off the step at (8, 16, 1024, 72)).
 // Direct, in row order, and in row order without allocation, us: full
 // (32, 16, 405, 72) 49.0, 49.7, 46.4; refresh (8, 16, 1024, 72) 78.8, 79.3,
 // 74.2, (16, 16, 700, 64) 74.1, 73.0, 66.9; reuse (2, 16, 4096, 72) 68.5, 67.4,
@@ -1230,12 +1230,12 @@ __global__ void __launch_bounds__(NTHREADS)
 // help there.
 // ---------------------------------------------------------------------------
 
-// One query block's state as a wavefront leaves it in LDS: 16 bytes per lane
-// and output block, then (-m - P_SHIFT, threshold, row-sum share).
 // Wavefronts per SIMD that its register budget allows for.
 template <int KMODE, int KS>
 constexpr int keysplit_waves() { return KMODE == MODE_REFRESH ? KS : 4; }
 
+// One query block's state as a wavefront leaves it in LDS: 16 bytes per lane
+// and output block, then (-m - P_SHIFT, threshold, row-sum share).
 template <int D>
 constexpr int state_elems() { return (Geo<D>::NDB + 1) * 64 * 8; }
 
