@@ -1246,11 +1246,13 @@ __device__ __forceinline__ void put_state(const Acc<D, 1>& a, uint16_t* at, int 
     *(f32x4*)(at + (Geo<D>::NDB * 64 + lane) * 8) = f32x4{a.negm[0], a.thr[0], a.l[0], 0.f};
 }
 
-// a += the state at `at`, both scaled to the larger running maximum
+// a += the state at `at`, both scaled to the larger running maximum.  A state
+// without a maximum saw no key of these queries, and is zero, or only scores
+// that set none (NaN, -inf): its accumulator may then hold a NaN, which a
+// factor of 0 passes on, so no state is skipped.
 template <int D>
 __device__ __forceinline__ void add_state(Acc<D, 1>& a, const uint16_t* at, int lane, float c) {
     const f32x4 st = *(const f32x4*)(at + (Geo<D>::NDB * 64 + lane) * 8);
-    if (__all(st[1] == NEG_INF)) return;   // it saw no key of these queries
     const float ma = a.running_max(0), mb_ = st[1] == NEG_INF ? NEG_INF : -(st[0] + P_SHIFT);
     const float m = fmaxf(ma, mb_);
     const float sa = ma == NEG_INF ? 0.f : __builtin_amdgcn_exp2f(ma - m);

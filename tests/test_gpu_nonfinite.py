@@ -1,0 +1,62 @@
+"""Non-finite keys: a query that attends a NaN or infinite score gives what
+float64 attention gives (NaN wherever that is NaN, finite elsewhere), whichever
+form of the attention kernels a launch takes and however its keys are dealt to
+wavefronts; a key outside the band stays out of the window attention."""
+import pytest
+import torch
+
+from paper_2406_08552_amd import dfa
+from tests.test_gpu_keysplit import _attn64
+from tests.test_gpu_parity import say
+
+pytestmark = pytest.mark.gpu
+
+
+def _same_nans(name, got, ref):
+    a, b = torch.isnan(got.double()), torch.isnan(ref)
+    assert torch.equal(a, b), f"{name}: {int((a & ~b).sum())} NaN too many, {int((b & ~a).sum())} lost"
+
+
+def _tiles(*ts):
+    return [k for t in ts for k in range(64 * t, 64 * t + 64)]
+
+
+# (B, H, L, d, w, keys): lengths of 64 k + 1, so that the last key is alone in
+# its tile; `keys` is all that one group of wavefronts sees
+KEY_GROUPS = [
+    (1, 4, 65, 72, 20, [64]),                               # refresh, two groups
+    (1, 4, 65, 64, 20, [64]),
+    (1, 2, 449, 72, 70, _tiles(3) + [-1]),                  # full and refresh: the last of four and of two groups
+    (1, 2, 513, 64, 200, _tiles(0, 4) + [512]),             # the first group of four
+    (1, 1, 577, 72, 90, _tiles(1, 3, 5, 7)),                # the second of two, and two of four
+    (1, 17, 961, 72, 200, _tiles(*range(1, 15, 2))),        # 272 workgroups: two groups
+    (1, 2, 1025, 72, 161, [1024]),                          # the last window's fourth group
+    (1, 2, 1025, 64, 161, [1024]),
+]
+
+
+@pytest.mark.parametrize("B,H,L,d,w,keys", KEY_GROUPS)
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_key_groups_keep_nonfinite_scores(B, H, L, d, w, keys, value):
+    _check_all(B, H, L, d, w, keys, value)
+
+
+def _check_all(B, H, L, d, w, keys, value):
+    dev = torch.device("cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L + d)
+    Q, K, V = (torch.randn((B, H, L, d), generator=g, device=dev).to(torch.bfloat16) for _ in range(3))
+    K[:, :, keys, 5] = value       # an infinite key scores +inf or -inf by the sign of the query's dim
+    say(f"non-finite keys B={B} H={H} L={L} d={d} w={w} n={len(keys)} value={value}")
+    full, win = _attn64(Q.double(), K.double(), V.double()), _attn64(Q.double(), K.double(), V.double(), w)
+    O, R = torch.empty_like(Q), torch.empty((B, H, L, d), device=dev)
+    dfa.dfa_attn_full(Q, K, V, O)
+    torch.cuda.synchronize()
+    _same_nans("full", O, full)
+    dfa.dfa_attn_window_plus_residual(Q, K, V, O, None, w)
+    torch.cuda.synchronize()
+    _same_nans("window", O, win)
+    dfa.dfa_attn_full_and_residual(Q, K, V, O, R, w)
+    torch.cuda.synchronize()
+    _same_nans("refresh O", O, full)
+    _same_nans("refresh R", R, full - win)
