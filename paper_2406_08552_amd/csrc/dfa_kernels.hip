@@ -918,14 +918,17 @@ __device__ __forceinline__ void store_residual(const Params& p, const f32x4 (&o)
 // from its own running max to the larger one, R = O - W.
 template <int D, int QB>
 __device__ __forceinline__ void store_split(const Params& p, const Acc<D, QB>& aw, const Acc<D, QB>& ax, size_t head_off,
-                                            int qw0, int L, uint16_t* Wl, int lane) {
+                                            int qw0, int L, int w, uint16_t* Wl, int lane) {
     using G = Geo<D>;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const int q0 = qw0 + 16 * qb;
         // row sums first: they exchange values across lanes
         const float lw = row_sum<D>(aw, qb, lane & 15), lx = row_sum<D>(ax, qb, lane & 15);
-        const bool has_x = ax.thr[qb] != NEG_INF;
+        // whether the query has keys outside its band (not whether ax has a
+        // maximum: it has none if all of their scores are NaN)
+        const int qi = q0 + (lane & 15);
+        const bool has_x = qi > w || qi < L - 1 - w;
         const float mw = aw.running_max(qb);
         const float mx = ax.running_max(qb);
         const float mm = fmaxf(mw, mx);
@@ -965,7 +968,7 @@ __device__ __forceinline__ void refresh_split(const Params& p, uint16_t* smem, W
     wait_vm_all();
     __syncthreads();
     wk.run_split(aw, ax, q, 0, ntiles);
-    if (wk.wave_active) store_split<D, QB>(p, aw, ax, head_off, wk.qw0, wk.L, smem + (wk.tid >> 6) * 2 * OUT_ELEMS, wk.tid & 63);
+    if (wk.wave_active) store_split<D, QB>(p, aw, ax, head_off, wk.qw0, wk.L, wk.w, smem + (wk.tid >> 6) * 2 * OUT_ELEMS, wk.tid & 63);
 }
 
 template <int D, int KMODE, int QB>
@@ -1370,7 +1373,7 @@ attn_keysplit_kernel(Params p) {
         if constexpr (MODE == MODE_REFRESH) add_state<D>(ax, states + (k * NACC + 1) * STATES, lane, p.c);
     }
     if constexpr (MODE == MODE_REFRESH) {
-        store_split<D, 1>(p, acc, ax, head_off, qw0, L, smem + STATE0 + (KS - 1) * NACC * STATES + wave * 2 * OUT_ELEMS, lane);
+        store_split<D, 1>(p, acc, ax, head_off, qw0, L, w, smem + STATE0 + (KS - 1) * NACC * STATES + wave * 2 * OUT_ELEMS, lane);
     } else {
         const float inv = 1.f / row_sum<D>(acc, 0, r);
         const float* rl = (const float*)(smem + (iters & 1) * G::STAGE_ELEMS) + (wave * 16 + r) * D;

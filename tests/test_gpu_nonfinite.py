@@ -41,6 +41,32 @@ def test_key_groups_keep_nonfinite_scores(B, H, L, d, w, keys, value):
     _check_all(B, H, L, d, w, keys, value)
 
 
+# One-pass refreshes (more than 256 workgroups of 64 queries, and two key
+# groups): the first and last query have one key outside their band
+@pytest.mark.parametrize("B,H,L,d,w,keys", [
+    (2, 16, 577, 72, 575, [576]),
+    (2, 16, 577, 64, 575, [0]),
+    (2, 7, 1280, 64, 1278, [1279]),
+    (2, 2, 257, 72, 255, [256]),
+    (1, 4, 65, 64, 63, [64]),
+    (1, 2, 200, 72, 40, list(range(110, 200))),     # all keys outside the bands of the first queries' wavefronts and more
+])
+def test_refresh_keeps_nan_outside_the_band(B, H, L, d, w, keys):
+    _check_all(B, H, L, d, w, keys, float("nan"))
+
+
+# the other forms: short sequences, narrow bands, two phases
+@pytest.mark.parametrize("B,H,L,d,w,keys", [
+    (1, 2, 16, 72, 2, [15]),
+    (1, 2, 31, 64, 20, [0]),
+    (1, 2, 100, 72, 5, [99]),
+    (2, 16, 1409, 64, 300, [1408]),
+    (4, 16, 1300, 72, 1298, [0]),
+])
+def test_other_forms_keep_nan(B, H, L, d, w, keys):
+    _check_all(B, H, L, d, w, keys, float("nan"))
+
+
 def _check_all(B, H, L, d, w, keys, value):
     dev = torch.device("cuda")
     g = torch.Generator(device="cuda")
