@@ -35,6 +35,13 @@
  *            tokens) add the bf16 rounding residual of each probability as a
  *            second PV operand: with so few keys the rounding of the weights
  *            does not average out.
+ *   Bits     Equal calls give equal bits.  The order of a query's sums follows
+ *            from the sizes of the call, B and H included, so a batch entry
+ *            computed in a call of another batch size may differ in its last
+ *            bit.  Bit for bit equal are: the conditional half under an ASC
+ *            code and under the whole-batch code (same B); full attention and
+ *            window attention with w >= L-1; the projections of a token,
+ *            whatever the call's other tokens.
  *   CFG      A classifier-free-guidance batch holds B = 2P entries: entries
  *            0..P-1 are the conditional evaluations and entry b + P is the
  *            unconditional partner of entry b (Sec. 3.4).

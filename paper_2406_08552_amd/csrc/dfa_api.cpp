@@ -107,6 +107,7 @@ dfa::AttnLaunch make_launch(const void* Q, const void* K, const void* V, const S
     a.K = K;
     a.V = V;
     a.B = s.B;
+    a.Bcall = s.B;
     a.H = s.H;
     a.L = s.L;
     a.d = s.d;

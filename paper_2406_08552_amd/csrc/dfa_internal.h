@@ -19,6 +19,7 @@ struct AttnLaunch {
     void* dst[4];
     int ndst;
     int B, H, L, d, w;
+    int Bcall;         // batch of the whole call (B, or twice it when the launch is its conditional half)
     bool read_next;    // the next launch reads the outputs: they are stored with allocation in L2
 };
 

@@ -1411,6 +1411,28 @@ __global__ void __launch_bounds__(256) copy16_kernel(const u32x4* __restrict__ s
     }
 }
 
+// One query block per wavefront (64-query workgroups, four wavefronts per
+// SIMD) when a workgroup's tile walk is short: the extra workgroups and
+// wavefronts hide latency there.  Long walks run faster with two blocks,
+// which halve the K/V tile copies per query.  The crossovers, measured at
+// d = 72 with interleaved timings: full attention up to L = 256 (4 key tiles),
+// window attention up to a band of 1280 keys.  A band that covers every key is
+// full attention and takes full attention's choice, so that the two give
+// identical results.  The refresh has one block up to L = 1280 in its split
+// form (launch_refresh) and two beyond.
+template <int MODE>
+bool one_query_block(const AttnLaunch& a, int B) {
+    // A launch whose 128-query workgroups would number at most one per CU
+    // (one wavefront per SIMD) takes 64-query workgroups whatever its length:
+    // measured 11% faster at (B, H, L) = (1, 16, 2048) and (4, 16, 512).
+    if ((long long)B * a.H * ((a.L + bq<2>() - 1) / bq<2>()) <= 256) return true;
+    if constexpr (MODE == MODE_REFRESH) return false;
+    if constexpr (MODE == MODE_WINDOW) {
+        if (a.w < a.L - 1) return 2LL * a.w + 1 <= 1280;
+    }
+    return a.L <= 256;
+}
+
 // Key groups of a launch of 64-query workgroups (1: attn_kernel).  Two
 // workgroups of four wavefronts per CU are two wavefronts per SIMD; below that
 // the groups fill the SIMDs.  Combining them costs about 1 us, so a walk of
@@ -1420,9 +1442,17 @@ __global__ void __launch_bounds__(256) copy16_kernel(const u32x4* __restrict__ s
 // tiles 18.6 and 15.8; at 512 workgroups full attention of 16 tiles 19.8 us in
 // one, 18.9 in two).  A refresh, whose walk also carries two accumulators'
 // work, gains from 2 tiles on (4 tiles 10.6 -> 9.2 us, 64 tiles 57.9 -> 44.0);
-// its registers allow two groups and no more than 256 workgroups.
+// its registers allow two groups and no more than 256 workgroups.  The groups
+// change the order of a query's sums, so their number is that of the whole
+// call's batch also where only its conditional half is launched: the ASC codes
+// then give the conditional half of the whole-batch code bit for bit.  Against
+// groups by the half's own workgroups, us: refresh half of (2, 16, 1024, 72)
+// 15.8 -> 18.9, full half of (2, 16, 2048, 72) 29.5 -> 31.5 (in one group 22.1
+// and 35.9).
 template <int MODE>
-int key_groups(const AttnLaunch& a, long long nblocks) {
+int key_groups(const AttnLaunch& a) {
+    if (MODE != MODE_REFRESH && !one_query_block<MODE>(a, a.Bcall)) return 1;
+    const long long nblocks = (long long)a.Bcall * a.H * ((a.L + bq<1>() - 1) / bq<1>());
     long long tiles = (a.L + BK - 1) / BK;
     if (MODE == MODE_REFRESH) return nblocks <= 256 && tiles >= 2 ? 2 : 1;
     if (MODE == MODE_WINDOW) {
@@ -1457,7 +1487,7 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
                   "one workgroup per wave slot of a SIMD must fit in LDS");
     if constexpr (QB == 1 && MODE != MODE_WINDOW_FINE && MODE != MODE_REFRESH_FINE) {
         constexpr int KM = MODE == MODE_REFRESH_SPLIT ? MODE_REFRESH : MODE;
-        const int ks = key_groups<KM>(a, nb);
+        const int ks = key_groups<KM>(a);
         if constexpr (KM != MODE_REFRESH) {
             if (ks == 4) {
                 hipLaunchKernelGGL((attn_keysplit_kernel<D, KM, 4>), dim3(p.nblocks), dim3(4 * NTHREADS), 0, stream, p);
@@ -1473,31 +1503,9 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// One query block per wavefront (64-query workgroups, four wavefronts per
-// SIMD) when a workgroup's tile walk is short: the extra workgroups and
-// wavefronts hide latency there.  Long walks run faster with two blocks,
-// which halve the K/V tile copies per query.  The crossovers, measured at
-// d = 72 with interleaved timings: full attention up to L = 256 (4 key tiles),
-// window attention up to a band of 1280 keys.  A band that covers every key is
-// full attention and takes full attention's choice, so that the two give
-// identical results.  The refresh has one block up to L = 1280 in its split
-// form (launch_refresh) and two beyond.
-template <int MODE>
-bool one_query_block(const AttnLaunch& a) {
-    // A launch whose 128-query workgroups would number at most one per CU
-    // (one wavefront per SIMD) takes 64-query workgroups whatever its length:
-    // measured 11% faster at (B, H, L) = (1, 16, 2048) and (4, 16, 512).
-    if ((long long)a.B * a.H * ((a.L + bq<2>() - 1) / bq<2>()) <= 256) return true;
-    if constexpr (MODE == MODE_REFRESH) return false;
-    if constexpr (MODE == MODE_WINDOW) {
-        if (a.w < a.L - 1) return 2LL * a.w + 1 <= 1280;
-    }
-    return a.L <= 256;
-}
-
 template <int MODE>
 hipError_t launch_mode(const AttnLaunch& a, hipStream_t stream) {
-    const bool one = one_query_block<MODE>(a);
+    const bool one = one_query_block<MODE>(a, a.B);
     switch (a.d) {
         case 64: return one ? launch_attn<64, MODE, 1>(a, stream) : launch_attn<64, MODE, 2>(a, stream);
         case 72: return one ? launch_attn<72, MODE, 1>(a, stream) : launch_attn<72, MODE, 2>(a, stream);
