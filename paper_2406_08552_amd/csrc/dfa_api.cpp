@@ -112,6 +112,7 @@ dfa::AttnLaunch make_launch(const void* Q, const void* K, const void* V, const S
     a.L = s.L;
     a.d = s.d;
     a.w = s.w;
+    a.nout = 1;
     return a;
 }
 
@@ -236,6 +237,7 @@ dfa_status dfa_plan_step(int code, const void* Q, const void* K, const void* V, 
         const size_t half = s.bytes / 2;
         a.B = B / 2;
         a.dst[a.ndst++] = (char*)O + half;
+        a.nout = 2;
         if (sep) {
             a.dst[a.ndst++] = Ocache;
             a.dst[a.ndst++] = (char*)Ocache + half;
@@ -421,7 +423,6 @@ dfa_status dfa_module_step(int code, const void* X, const void* Wqkv, const void
     if ((st = hip_status(dfa::launch_qkv_proj(pq, stream), "QKV projection launch")) != DFA_OK) return st;
 
     dfa::AttnLaunch a = make_launch(Q, K, V, s);
-    a.read_next = true;   // by the output projection
     a.B = Bc;
     a.dst[0] = O;
     a.ndst = 1;

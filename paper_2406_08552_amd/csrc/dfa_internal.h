@@ -18,9 +18,9 @@ struct AttnLaunch {
     void* Rout;        // refresh kernel: fp32 residual output
     void* dst[4];
     int ndst;
+    int nout;          // the first nout of dst[] are O, which a caller's next launch reads; the others its output cache
     int B, H, L, d, w;
     int Bcall;         // batch of the whole call (B, or twice it when the launch is its conditional half)
-    bool read_next;    // the next launch reads the outputs: they are stored with allocation in L2
 };
 
 // One projection launch of the attention module over B * L tokens.

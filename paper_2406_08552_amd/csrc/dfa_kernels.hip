@@ -170,7 +170,7 @@ struct Params {
     int n_qt;                 // query tiles per (batch, head)
     int nblocks;
     float c;                  // log2(e) / sqrt(d)
-    int read_next;            // store O with allocation in L2
+    int nout;                 // the first nout of dst[] are O, the others the output cache
 };
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -852,14 +852,14 @@ constexpr int OUT_ELEMS = 16 * OUT_PITCH;   // bf16 elements of a wavefront's ro
 // of them, from row offset `at`.  A lane holds 4 dims of one query, so stores
 // straight from it write 32-byte (bf16) or 64-byte (fp32) pieces of 16 rows;
 // passed through LDS `Wl` (the wavefront's own), they leave as whole lines in
-// row order, without allocation in L2 (nothing in the launch reads them again;
-// in a module step the next launch does, and there they are allocated, which
-// takes 2% off the step at (8, 16, 1024, 72)).
-// Direct, in row order, and in row order without allocation, us: full
-// (32, 16, 405, 72) 49.0, 49.7, 46.4; refresh (8, 16, 1024, 72) 78.8, 79.3,
-// 74.2, (16, 16, 700, 64) 74.1, 73.0, 66.9; reuse (2, 16, 4096, 72) 68.5, 67.4,
-// 64.7, (8, 16, 1024, 72) 33.6, 33.3, 30.5.  Direct without allocation, pieces
-// of lines, is slower than all three (55.3, 86.7, 74.8, 72.9, 40.9).
+// row order.  O is allocated in the caches, since a caller's next launch (the
+// output projection) reads it; its cache and R, which a later step reads, are
+// not.  O without allocation takes 1-2 us off the call and puts 6-7 on the
+// projection behind it, us of the call, then of both, without and with: full
+// (810, 16, 16, 72) 23.4, 24.8 and 72.5, 65.6; (32, 16, 405, 72) 46.8, 47.9
+// and 97.4, 90.2; reuse (8, 16, 1024, 72) 33.0, 33.8 and 67.6, 61.1; from
+// 75 MB of O on the pairs are level.  R in whole lines without allocation,
+// against direct stores: refresh (8, 16, 1024, 72) 82.9 -> 76.7.
 template <int D>
 __device__ __forceinline__ void store_rows(const Params& p, const u32x2 (&o)[Geo<D>::NDB], uint16_t* Wl, size_t at, int rows,
                                            int lane) {
@@ -878,23 +878,21 @@ __device__ __forceinline__ void store_rows(const Params& p, const u32x2 (&o)[Geo
         v[it] = u32x4{0u, 0u, 0u, 0u};
         if (idx < 16 * G::NCH) v[it] = *(const u32x4*)(Wl + row * OUT_PITCH + 8 * ch);
     }
-    for (int di = 0; di < p.ndst; ++di) {
+    for (int di = 0; di < p.nout; ++di) {
         u32x4* out = (u32x4*)(p.dst[di] + at);
 #pragma unroll
         for (int it = 0; it < NIT; ++it)
-            if (it * 64 + lane < rows * G::NCH) {
-                if (p.read_next) {
-                    asm volatile("" ::: "memory");   // on both sides: else the two forms are merged into the plain one
-                    out[it * 64 + lane] = v[it];
-                    asm volatile("" ::: "memory");
-                } else {
-                    __builtin_nontemporal_store(v[it], out + it * 64 + lane);
-                }
-            }
+            if (it * 64 + lane < rows * G::NCH) out[it * 64 + lane] = v[it];
+    }
+    for (int di = p.nout; di < p.ndst; ++di) {
+        u32x4* out = (u32x4*)(p.dst[di] + at);
+#pragma unroll
+        for (int it = 0; it < NIT; ++it)
+            if (it * 64 + lane < rows * G::NCH) __builtin_nontemporal_store(v[it], out + it * 64 + lane);
     }
 }
 
-// The same for the residual, fp32.
+// The same for the residual, fp32, without allocation.
 template <int D>
 __device__ __forceinline__ void store_residual(const Params& p, const f32x4 (&o)[Geo<D>::NDB], uint16_t* Wl, size_t at,
                                                int rows, int lane) {
@@ -1473,7 +1471,7 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
     p.Rin = (const float*)a.Rin;
     p.Rout = (float*)a.Rout;
     p.ndst = a.ndst;
-    p.read_next = a.read_next;
+    p.nout = a.nout;
     for (int i = 0; i < 4; ++i) p.dst[i] = (uint16_t*)(i < a.ndst ? a.dst[i] : nullptr);
     p.H = a.H;
     p.L = a.L;

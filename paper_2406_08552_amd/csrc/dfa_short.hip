@@ -29,11 +29,12 @@
 // query, so a store straight from it writes 32-byte pieces of 16 rows.  The
 // outputs (and a refresh's R at d = 72, whose 288-byte rows straddle lines)
 // instead pass through the wavefront's LDS rows, which V has left, and leave
-// as whole lines in row order, without allocation in L2 (nothing here reads
-// them again; in a module step the next launch does, and O is allocated).  Direct, in row order, and in row order without allocation, at
-// 12960 sequences of (16, 72): full 28.1, 24.7, 20.6 us; window with R 39.8,
-// 35.8, 33.7 us; refresh 43.9, 40.2, 31.1 us.  Stores without allocation of
-// pieces of a line are the slowest of all (L = 32 refresh 13.1 -> 19.8 us).
+// as whole lines in row order.  O is allocated in the caches, since a caller's
+// next launch (the output projection) reads it; its cache and R, which a later
+// step reads, are not.  Direct, in row order, and in row order without
+// allocation, at 12960 sequences of (16, 72): full 28.1, 24.7, 23.4 us (with the
+// output projection behind it 65.6 allocated, 72.5 not); window with R 39.8,
+// 35.9, 34.0 us (77.4, 84.2); refresh 43.8, 36.1 us with R alone unallocated.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -83,7 +84,7 @@ struct SParams {
     float* Rout;              // MODE_REFRESH: fp32 residual output
     uint16_t* dst[4];         // every destination receives the same output
     int ndst;
-    int read_next;            // store O with allocation in L2
+    int nout;                 // the first nout of dst[] are O, the others the output cache
     int nseq;                 // B * H sequences of L tokens
     int L, w;
     float c;                  // log2(e) / sqrt(d)
@@ -365,19 +366,17 @@ short_attn_kernel(SParams p) {
         ov[it] = u32x4{0u, 0u, 0u, 0u};
         if (idx < L * G::NCH) ov[it] = *(const u32x4*)(Vl + row * G::OP + 8 * ch);
     }
-    for (int di = 0; di < p.ndst; ++di) {
+    for (int di = 0; di < p.nout; ++di) {
         u32x4* out = (u32x4*)(p.dst[di] + off);
 #pragma unroll
         for (int it = 0; it < OIT; ++it)
-            if (it * 64 + lane < L * G::NCH) {
-                if (p.read_next) {
-                    asm volatile("" ::: "memory");   // on both sides: else the two forms are merged into the plain one
-                    out[it * 64 + lane] = ov[it];
-                    asm volatile("" ::: "memory");
-                } else {
-                    __builtin_nontemporal_store(ov[it], out + it * 64 + lane);
-                }
-            }
+            if (it * 64 + lane < L * G::NCH) out[it * 64 + lane] = ov[it];
+    }
+    for (int di = p.nout; di < p.ndst; ++di) {
+        u32x4* out = (u32x4*)(p.dst[di] + off);
+#pragma unroll
+        for (int it = 0; it < OIT; ++it)
+            if (it * 64 + lane < L * G::NCH) __builtin_nontemporal_store(ov[it], out + it * 64 + lane);
     }
 }
 
@@ -390,7 +389,7 @@ hipError_t launch_short_attn(const AttnLaunch& a, hipStream_t stream) {
     p.Rin = (const float*)a.Rin;
     p.Rout = (float*)a.Rout;
     p.ndst = a.ndst;
-    p.read_next = a.read_next;
+    p.nout = a.nout;
     for (int i = 0; i < 4; ++i) p.dst[i] = (uint16_t*)(i < a.ndst ? a.dst[i] : nullptr);
     const long long nseq = (long long)a.B * a.H;
     const long long nblocks = (nseq + SW - 1) / SW;
