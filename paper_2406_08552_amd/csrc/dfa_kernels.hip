@@ -969,7 +969,7 @@ __device__ __forceinline__ void refresh_split(const Params& p, uint16_t* smem, W
     if (wk.wave_active) store_split<D, QB>(p, aw, ax, head_off, wk.qw0, wk.L, wk.w, smem + (wk.tid >> 6) * 2 * OUT_ELEMS, wk.tid & 63);
 }
 
-template <int D, int KMODE, int QB>
+template <int D, int KMODE, int QB, bool ROWS>
 __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
     using G = Geo<D>;
     constexpr int MODE = KMODE == MODE_ASC             ? MODE_FULL
@@ -1145,22 +1145,14 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
 
     if (!wk.wave_active) return;
 
-    // epilogue: normalise, form R, store bf16 to every destination.  The rows
-    // pass through the stage that holds no residual rows (both stages are free
-    // after the walk's last barrier), except in the two-phase refresh with two
-    // query blocks: at d = 72 it has no registers left for it (nine spills; 148 ->
-    // 152 us at (8, 16, 1500, 72)), at d = 64 it gained less than 1%.
-    constexpr bool DIRECT = MODE == MODE_REFRESH && QB == 2;
+    // epilogue: normalise, form R, store bf16 to every destination, through LDS
+    // as whole lines (ROWS) or straight from the registers
     static_assert(NWAVES * OUT_ELEMS <= G::STAGE_ELEMS && NWAVES * 2 * OUT_ELEMS <= 2 * G::STAGE_ELEMS, "output rows must fit");
-    uint16_t* Wl = MODE == MODE_REFRESH ? smem + wave * 2 * OUT_ELEMS
-                                        : smem + (wk.stage ^ 1) * G::STAGE_ELEMS + wave * OUT_ELEMS;
-    int el = tid;   // opaque: nothing of the epilogue's addressing is formed before the walk
-    asm volatile("" : "+v"(el));
-    el &= 63;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const int qrow = qw0 + 16 * qb + r;
         const float inv = 1.f / row_sum<D>(acc, qb, r);
+        if (!ROWS && qrow >= L) continue;
         const size_t row_off = head_off + (size_t)qrow * D;
         f32x4 res[G::NDB];
         u32x2 ob[G::NDB];
@@ -1170,9 +1162,7 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
 #pragma clang fp contract(off)
             const int col = 16 * mb + 4 * g;
             const bool ok = qrow < L && col < D;
-            if constexpr (DIRECT) {
-                if (!ok) continue;
-            }
+            if (!ROWS && !ok) continue;
             const size_t off = row_off + col;
             const f32x4 o = acc.o[qb][mb] * inv;
             f32x4 out = o;
@@ -1181,7 +1171,7 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
                 // band covering every key gives R == 0 exactly); the window
                 // result parked above is read back by the lane that wrote it.
                 res[mb] = o;
-                if (DIRECT || ok) res[mb] = o - *(const f32x4*)(p.Rout + off);
+                if (ok) res[mb] = o - *(const f32x4*)(p.Rout + off);
             }
             if constexpr (MODE == MODE_WINDOW) {
                 if (wk.rpre) {
@@ -1193,16 +1183,22 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
                 }
             }
             ob[mb] = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
-            if constexpr (DIRECT) {
-                *(f32x4*)(p.Rout + off) = res[mb];
+            if constexpr (!ROWS) {
+                if constexpr (MODE == MODE_REFRESH) *(f32x4*)(p.Rout + off) = res[mb];
                 for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + off) = ob[mb];
             }
         }
-        if constexpr (!DIRECT) {
+        if constexpr (ROWS) {
+            // through the stage that holds no residual rows (both stages are
+            // free after the walk's last barrier)
+            uint16_t* Wl = MODE == MODE_REFRESH ? smem + wave * 2 * OUT_ELEMS
+                                                : smem + (wk.stage ^ 1) * G::STAGE_ELEMS + wave * OUT_ELEMS;
+            int el = tid;   // opaque: nothing of the stores' addressing is formed before the walk
+            asm volatile("" : "+v"(el));
             const size_t at = head_off + (size_t)(qw0 + 16 * qb) * D;
             const int rows = min(16, L - (qw0 + 16 * qb));
-            if constexpr (MODE == MODE_REFRESH) store_residual<D>(p, res, Wl, at, rows, el);
-            store_rows<D>(p, ob, Wl, at, rows, el);
+            if constexpr (MODE == MODE_REFRESH) store_residual<D>(p, res, Wl, at, rows, el & 63);
+            store_rows<D>(p, ob, Wl, at, rows, el & 63);
         }
     }
 }
@@ -1215,11 +1211,11 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
 template <int D, int QB, int KMODE>
 constexpr int waves_per_simd() { return QB == 1 && (D == 64 || !split_refresh<KMODE>()) ? 4 : 3; }
 
-template <int D, int MODE, int QB>
+template <int D, int MODE, int QB, bool ROWS>
 __global__ void __launch_bounds__(NTHREADS)
     __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, QB, MODE>(), waves_per_simd<D, QB, MODE>()))) attn_kernel(Params p) {
     __shared__ __attribute__((aligned(16))) uint16_t smem[2 * Geo<D>::STAGE_ELEMS];
-    attn_body<D, MODE, QB>(p, smem);
+    attn_body<D, MODE, QB, ROWS>(p, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1461,6 +1457,22 @@ int key_groups(const AttnLaunch& a) {
     return nblocks <= 256 ? 4 : (nblocks <= 512 ? 2 : 1);
 }
 
+// Whether full and window outputs leave as whole lines, through LDS: with
+// several destinations (full (8, 16, 1024, 72) with a cache 56.7 -> 53.6 us,
+// reuse (32, 16, 405, 72) 51.8 -> 47.7), and in launches of 64-query workgroups
+// that write more O than the caches keep beside its inputs (direct and rows on
+// rotating buffers, then on two sets: reuse, 60 MB of O (64, 16, 405, 72) 82.3,
+// 79.0 and 81.7, 79.1 us; 23 MB (16, 16, 700, 64) 39.3, 38.6 and 35.5, 34.9;
+// 19 MB (8, 16, 1024, 72) 34.2, 33.8 and 28.0, 28.5; 4.7 MB (8, 16, 256, 72)
+// 9.84, 10.08 and 9.04, 9.32; (2, 16, 128, 72) 6.13, 6.27 and 5.63, 5.77).  Long
+// walks of 128-query workgroups gain nothing (reuse (2, 16, 8192, 72) 188,
+// 192).  One kernel with both forms in it was slower than either (9.17 us at
+// (8, 16, 256, 72)) and spilled in full attention at d = 72.
+template <int QB>
+bool store_as_rows(const AttnLaunch& a) {
+    return a.ndst > 1 || (QB == 1 && (size_t)a.B * a.H * a.L * a.d * 2 > (size_t)20 << 20);
+}
+
 template <int D, int MODE, int QB>
 hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
     using G = Geo<D>;
@@ -1497,7 +1509,16 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((attn_kernel<D, MODE, QB>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
+    if constexpr (MODE == MODE_FULL || MODE == MODE_WINDOW || MODE == MODE_WINDOW_FINE) {
+        if (store_as_rows<QB>(a)) hipLaunchKernelGGL((attn_kernel<D, MODE, QB, true>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
+        else hipLaunchKernelGGL((attn_kernel<D, MODE, QB, false>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
+    } else {
+        // ASC has several destinations, and R of a refresh passes through LDS as
+        // well; but the two-phase refresh with two query blocks has no registers
+        // left for it at d = 72 (nine spills; 148 -> 152 us at (8, 16, 1500, 72)),
+        // and at d = 64 it gained less than 1%
+        hipLaunchKernelGGL((attn_kernel<D, MODE, QB, MODE == MODE_ASC || QB == 1>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
+    }
     return hipGetLastError();
 }
 

@@ -14,9 +14,11 @@ pytestmark = pytest.mark.gpu
 
 # short kernel (one and two blocks, whole and ragged), 64-query workgroups with
 # and without key groups, 128-query workgroups; the second block of a wavefront
-# whole, of one row and empty
+# whole, of one row and empty; more than 20 MiB of O, where one destination of a
+# short walk is stored like several
 @pytest.mark.parametrize("B,H,L", [(6, 3, 1), (4, 5, 9), (2, 9, 16), (2, 3, 17), (4, 7, 32), (2, 3, 33), (2, 2, 79), (2, 16, 320),
-                                   (20, 16, 273), (20, 16, 384), (20, 16, 391), (2, 80, 1400)])
+                                   (20, 16, 273), (20, 16, 384), (20, 16, 391), (2, 80, 1400),
+                                   (32, 16, 405)])
 @pytest.mark.parametrize("d", [64, 72])
 def test_output_rows(B, H, L, d):
     dev = torch.device("cuda")
@@ -32,12 +34,16 @@ def test_output_rows(B, H, L, d):
         O.t.fill_(-7), C.t.fill_(-7)
         dfa.dfa_plan_step(code, Q, K, V, O.t, R.t, C.t, w)
         torch.cuda.synchronize()
+        one = torch.full_like(O.t, -7)   # one destination (two under ASC), without a cache
+        dfa.dfa_plan_step(code, Q, K, V, one, R.t, None, w)
+        torch.cuda.synchronize()
         n = B // 2 if half else B
         name = dfa.CODE_NAMES[code]
         _check(f"{name} O", O.t[:n].float(), full[:n])
         if half:
             assert torch.equal(O.t[n:], O.t[:n]), name
         assert torch.equal(C.t, O.t) or bool((C.t == -7).all()), name
+        assert torch.equal(one, O.t), name
         if res:
             _check(f"{name} R", R.t[:n], (full - win)[:n])
     assert O.guards_intact() and C.guards_intact() and R.guards_intact()
