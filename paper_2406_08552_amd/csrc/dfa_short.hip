@@ -27,14 +27,16 @@
 // HBM bandwidth bounds these kernels, and the shape of their stores decided
 // how much of it they reached.  The MFMA layout leaves a lane 4 dims of one
 // query, so a store straight from it writes 32-byte pieces of 16 rows.  The
-// outputs (and a refresh's R at d = 72, whose 288-byte rows straddle lines)
-// instead pass through the wavefront's LDS rows, which V has left, and leave
-// as whole lines in row order.  O is allocated in the caches, since a caller's
-// next launch (the output projection) reads it; its cache and R, which a later
-// step reads, are not.  Direct, in row order, and in row order without
-// allocation, at 12960 sequences of (16, 72): full 28.1, 24.7, 23.4 us (with the
-// output projection behind it 65.6 allocated, 72.5 not); window with R 39.8,
-// 35.9, 34.0 us (77.4, 84.2); refresh 43.8, 36.1 us with R alone unallocated.
+// outputs and a refresh's R instead pass through the wavefront's LDS rows, which
+// V has left, and leave as whole lines in row order.  O is allocated in the
+// caches, since a caller's next launch (the output projection) reads it; its
+// cache and R, which a later step reads, are not.  Direct, in row order, and in
+// row order without allocation, at 12960 sequences of (16, 72): full 28.1, 24.7,
+// 23.4 us (with the output projection behind it 65.6 allocated, 72.5 not);
+// window with R 39.8, 35.9, 34.0 us (77.4, 84.2); refresh 43.8, 36.1 us with R
+// alone unallocated.  At d = 64 R took, in pieces without allocation, plain
+// pieces and rows, 36.7, 35.5 and 32.1 us (L = 32, 6400 sequences: 37.6, 37.1
+// and 33.6).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -177,9 +179,8 @@ short_attn_kernel(SParams p) {
     using G = SGeo<D>;
     constexpr int MODE = KMODE == MODE_ASC ? MODE_FULL : KMODE;
     constexpr int ROWS = 16 * NB;
-    // a refresh at d = 72 sends R through LDS as well, as fp32 rows
-    constexpr bool R_ROWS = MODE == MODE_REFRESH && D == 72;
-    constexpr int WELEMS = ROWS * (R_ROWS ? 2 * D : G::VP);   // a wavefront's share
+    // a refresh sends R through LDS as well, as fp32 rows of the same pitch
+    constexpr int WELEMS = ROWS * (MODE == MODE_REFRESH ? 2 * G::OP : G::VP);   // a wavefront's share
     static_assert(WELEMS >= ROWS * G::VP, "V must fit");
     __shared__ __attribute__((aligned(16))) uint16_t smem[SW * WELEMS];
 
@@ -290,6 +291,7 @@ short_attn_kernel(SParams p) {
         }
     }
 
+    lds_fence();   // V is read: the outputs take its rows
     u32x2 ob[NB][G::NDB];   // the output, packed
 #pragma unroll
     for (int qb = 0; qb < NB; ++qb) {
@@ -331,10 +333,7 @@ short_attn_kernel(SParams p) {
             f32x4 out = ov;
             if constexpr (MODE == MODE_REFRESH) {
                 const f32x4 res = ov - o[NSET - 1][mb] * inv[NSET - 1];
-                if (qi < L && col < D) {
-                    if constexpr (R_ROWS) *(f32x4*)((float*)Vl + qi * D + col) = res;
-                    else __builtin_nontemporal_store(res, (f32x4*)(p.Rout + off + (size_t)qi * D + col));
-                }
+                if (qi < L && col < D) *(f32x4*)((float*)Vl + qi * G::OP + col) = res;
             }
             if constexpr (MODE == MODE_WINDOW) {
                 if (p.Rin) out = ov + rin[qb][mb];
@@ -343,12 +342,13 @@ short_attn_kernel(SParams p) {
         }
     }
 
-    if constexpr (R_ROWS) {
+    if constexpr (MODE == MODE_REFRESH) {
         lds_fence();
+        constexpr int N4 = D / 4;
 #pragma unroll
-        for (int it = 0; it < (ROWS * D / 4 + 63) / 64; ++it) {
-            const int c4 = it * 64 + lane;
-            if (c4 < L * (D / 4)) __builtin_nontemporal_store(*(const f32x4*)((const float*)Vl + c4 * 4), (f32x4*)(p.Rout + off) + c4);
+        for (int it = 0; it < (ROWS * N4 + 63) / 64; ++it) {
+            const int idx = it * 64 + lane, row = idx / N4, c4 = idx - row * N4;
+            if (idx < L * N4) __builtin_nontemporal_store(*(const f32x4*)((const float*)Vl + row * G::OP + 4 * c4), (f32x4*)(p.Rout + off) + idx);
         }
         lds_fence();
     }
