@@ -1,9 +1,10 @@
-"""Builds the C-ABI library ``libdfa.so`` (HIP kernels for gfx950 + host code)
-and ``_dfa_binding.so``, the native argument marshalling of its Python binding.
+"""Builds the C-ABI library ``libdfa.so`` (HIP kernels for gfx950 + host code;
+needs hipcc alone) and ``_dfa_binding.so``, the native argument marshalling of
+its Python binding (needs g++ and torch's headers).
 
-Both are compiled in-tree with hipcc; nothing is installed.  Every call
-of :func:`build_library` compiles again, so a changed source is always picked
-up.
+Both are compiled in-tree; nothing is installed.  Every call of
+:func:`build_library` and :func:`build_binding` compiles again, so a changed
+source is always picked up.
 """
 from __future__ import annotations
 
@@ -56,17 +57,16 @@ def _compile(cmd: list, path: str, verbose: bool) -> None:
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile every source into LIB_PATH (and the binding's marshalling into
-    BINDING_PATH) and return LIB_PATH."""
+    """Compile every source into LIB_PATH and return the path."""
     _compile([hipcc(), *HIPCC_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}", *[os.path.join(CSRC, s) for s in SOURCES]],
              LIB_PATH, verbose)
-    build_binding(verbose)
     return LIB_PATH
 
 
 def build_binding(verbose: bool = False) -> str:
-    """Compile the binding's argument marshalling (host code only; its symbols
-    of Python and torch come from the importing process)."""
+    """Compile the binding's argument marshalling into BINDING_PATH (host code
+    only; its symbols of Python and torch come from the importing process) and
+    return the path."""
     import torch
     from torch.utils import cpp_extension
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
@@ -80,3 +80,4 @@ def build_binding(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_binding(verbose=True))

@@ -6,8 +6,8 @@ reads B, H, L, d from the
 shapes, and calls the C function of the same name with the tensors' device
 pointers and the current HIP stream.  Ordinary calls on the current stream are
 marshalled by the native ``_dfa_binding`` (csrc/dfa_binding.cpp: 6.5 to 7 us of
-Python and ctypes work a call otherwise); it declines anything else (-1), and
-the Python code below then checks, raises or calls.  All computation happens in the
+Python and ctypes work a call otherwise), where it is built; it declines anything
+else (-1), and the Python code below then checks, raises or calls.  All computation happens in the
 library's HIP kernels; there is no fallback of any kind.  A non-OK status
 raises :class:`DfaError` with the library's message.
 
@@ -93,16 +93,23 @@ def lib() -> ctypes.CDLL:
 _NATIVE = None
 
 
+class _Declines:
+    """In place of the native marshalling: every call takes the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: -1
+
+
 def _native():
-    """The native marshalling, bound to this process's library; raises if it
-    is missing."""
+    """The native marshalling, bound to this process's library.  It is built
+    apart from the library; without it the general path makes every call."""
     global _NATIVE
     if _NATIVE is None:
         import importlib.util
         torch, L = _torch(), lib()   # torch first: the extension's symbols come from it
         if not os.path.exists(BINDING_PATH):
-            raise RuntimeError(f"{BINDING_PATH} is missing: build it first "
-                               "(python -c 'import __graft_entry__ as g; g.build()')")
+            _NATIVE = _Declines()
+            return _NATIVE
         spec = importlib.util.spec_from_file_location("_dfa_binding", BINDING_PATH)
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2406_08552_amd import dfa
+from paper_2406_08552_amd import build, dfa
 
 
 class _Sub(torch.Tensor):
@@ -31,6 +31,32 @@ def test_declines_unusual_arguments():
         dfa.dfa_plan_step(0, t, t, t, t, None, None, 3)
     with pytest.raises(TypeError, match="bf16|bfloat16"):
         dfa.dfa_attn_full(t.float(), t, t, t)
+
+
+def test_library_builds_with_hipcc_alone(monkeypatch):
+    made = []
+    monkeypatch.setattr(build, "_compile", lambda cmd, path, verbose: made.append((cmd[0], path)))
+    assert build.build_library() == build.LIB_PATH
+    assert made == [(build.hipcc(), build.LIB_PATH)]
+    assert build.build_binding() == build.BINDING_PATH
+    assert [p for _, p in made] == [build.LIB_PATH, build.BINDING_PATH]
+
+
+def test_calls_without_the_extension(monkeypatch, tmp_path):
+    """A library built alone is enough for the binding: its general path makes
+    the same checks and calls."""
+    monkeypatch.setattr(dfa, "BINDING_PATH", str(tmp_path / "missing.so"))
+    monkeypatch.setattr(dfa, "_NATIVE", None)
+    t = torch.zeros(1, 2, 64, 64, dtype=torch.bfloat16)
+    with pytest.raises(ValueError, match="GPU"):
+        dfa.dfa_plan_step(0, t, t, t, t, None, None, 3)
+    with pytest.raises(ValueError, match="GPU"):
+        dfa.dfa_attn_full(t, t, t, t)
+    if torch.cuda.is_available():
+        Q, K, V = (torch.randn(1, 2, 64, 64, device="cuda").to(torch.bfloat16) for _ in range(3))
+        O = torch.zeros_like(Q)
+        dfa.dfa_attn_full(Q, K, V, O)
+        assert bool(O.any())
 
 
 @pytest.mark.gpu
