@@ -102,12 +102,13 @@ class _Declines:
 
 def _native():
     """The native marshalling, bound to this process's library.  It is built
-    apart from the library; without it the general path makes every call."""
+    apart from the library and asks torch for the current stream; without it,
+    or in a torch without GPU support, the general path makes every call."""
     global _NATIVE
     if _NATIVE is None:
         import importlib.util
         torch, L = _torch(), lib()   # torch first: the extension's symbols come from it
-        if not os.path.exists(BINDING_PATH):
+        if not os.path.exists(BINDING_PATH) or not hasattr(torch._C, "_cuda_getCurrentRawStream"):
             _NATIVE = _Declines()
             return _NATIVE
         spec = importlib.util.spec_from_file_location("_dfa_binding", BINDING_PATH)

@@ -59,6 +59,16 @@ def test_calls_without_the_extension(monkeypatch, tmp_path):
         assert bool(O.any())
 
 
+def test_torch_without_gpu_support(monkeypatch):
+    """CPU tensors are refused with the general path's message there too."""
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        monkeypatch.delattr(torch._C, name)
+    monkeypatch.setattr(dfa, "_NATIVE", None)
+    t = torch.zeros(1, 2, 64, 64, dtype=torch.bfloat16)
+    with pytest.raises(ValueError, match="GPU"):
+        dfa.dfa_plan_step(0, t, t, t, t, None, None, 3)
+
+
 @pytest.mark.gpu
 def test_native_calls_match_the_general_path():
     dev = torch.device("cuda")
