@@ -65,15 +65,16 @@
 //   wavefront classifies the tile against its own queries (inside the band,
 //   outside, or straddling it with an element mask).
 //   The window kernel visits only the tiles that intersect the workgroup's
-//   band.  For L > 1280 the refresh kernel runs ONE accumulator over two
+//   band.  In long sequences the refresh kernel runs ONE accumulator over two
 //   phases: first the in-band scores of the band tiles (after which the
 //   accumulator, normalised, is the window attention W; it is parked in the R
 //   buffer), then every out-of-band score, which turns the same accumulator
 //   into full attention.  R = O - W is formed in the epilogue.  Every score is
 //   used exactly once, only the few band-edge tiles are visited twice, and no
-//   second accumulator occupies registers.  Up to L = 1280, where band-edge
-//   tiles are most of the walk, the refresh instead keeps two accumulators
-//   and visits every tile once (MODE_REFRESH_SPLIT).
+//   second accumulator occupies registers.  In shorter ones, where band-edge
+//   tiles are a large part of the walk (one_pass_refresh), and in launches of
+//   few workgroups, which take key groups, the refresh instead keeps two
+//   accumulators and visits every tile once.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -1412,15 +1413,15 @@ __global__ void __launch_bounds__(256) copy16_kernel(const u32x4* __restrict__ s
 // d = 72 with interleaved timings: full attention up to L = 256 (4 key tiles),
 // window attention up to a band of 1280 keys.  A band that covers every key is
 // full attention and takes full attention's choice, so that the two give
-// identical results.  The refresh has one block up to L = 1280 in its split
-// form (launch_refresh) and two beyond.
+// identical results.  A refresh has one block in its one-pass form
+// (one_pass_refresh), and up to L = 1024 in two phases.
 template <int MODE>
 bool one_query_block(const AttnLaunch& a, int B) {
     // A launch whose 128-query workgroups would number at most one per CU
     // (one wavefront per SIMD) takes 64-query workgroups whatever its length:
     // measured 11% faster at (B, H, L) = (1, 16, 2048) and (4, 16, 512).
     if ((long long)B * a.H * ((a.L + bq<2>() - 1) / bq<2>()) <= 256) return true;
-    if constexpr (MODE == MODE_REFRESH) return false;
+    if constexpr (MODE == MODE_REFRESH) return a.L <= 1024;
     if constexpr (MODE == MODE_WINDOW) {
         if (a.w < a.L - 1) return 2LL * a.w + 1 <= 1280;
     }
@@ -1538,12 +1539,39 @@ bool head_dim_supported(int d) { return d == 64 || d == 72; }
 
 hipError_t launch_full(const AttnLaunch& a, hipStream_t s) { return launch_mode<MODE_FULL>(a, s); }
 hipError_t launch_asc(const AttnLaunch& a, hipStream_t s) { return launch_mode<MODE_ASC>(a, s); }
-// Refresh: the one-pass two-accumulator form up to L = 1280 (20 key tiles),
-// where band-edge tiles, which the two-phase form visits twice, are a large
-// part of the walk, the two-phase form beyond.  Measured one-pass against
-// two-phase, us: (8, 16, 1024, 72) 79.2 and 86.0, (16, 16, 700, 64) 75.5 and
-// 92.6, (16, 4, 1300, 64) 61.6 and 64.5, (8, 16, 1500, 72) 161.5 and 150.4,
-// (4, 16, 2048, 64) 117.4 and 109.0.
+// Whether a refresh takes the one-pass two-accumulator form: where band-edge
+// tiles, which the two-phase form visits twice, are a large part of the walk.
+// Three things set its limit (times of two phases over one in brackets, B * H *
+// ceil(L / 64) = n workgroups of 64 queries; 1296 launches of 640 to 1280 tokens
+// were measured in both forms, of which the rule is never more than 5% slower
+// than two phases, which took all of them beyond 512 tokens before, and 11%
+// faster on average):
+//   - rounds.  One pass holds 1024 workgroups at once at d = 64, 768 at d = 72
+//     (three wavefronts per SIMD); two phases hold 1024, and beyond 1024 tokens
+//     768 of twice the queries, which leaves half a round of n <= 768 idle.
+//     d = 72: n = 576 of 1100 tokens (1.4 to 1.54), n = 832 of 800 (1.05, 0.98),
+//     1024 of 1024 (1.00 to 0.94), 1152 of 1024 (1.1 to 1.17), 1280 of 1280 (1.06
+//     to 1.14);
+//   - the band.  Nearly all keys in it leave two phases little more than full
+//     attention's work: d = 72, n = 2880 of 900 tokens, w = 675 (1.04), w = 898
+//     (0.98); beyond 1024 tokens from half the keys on, n = 2432 of 1216, w = 405
+//     (1.08), w = 608 (1.00), w = 1214 (0.88);
+//   - K/V copies per query, which two query blocks per wavefront halve: 1216
+//     tokens, w = 152, n = 2432 (1.10), 7296 (1.00); d = 64 (1.17) and (1.10).
+// As with the key groups, the whole call's batch decides.
+bool one_pass_refresh(const AttnLaunch& a) {
+    if (a.L <= 512) return true;
+    if (a.L > 1280) return false;
+    const long long n = (long long)a.Bcall * a.H * ((a.L + bq<1>() - 1) / bq<1>());
+    if (n <= (a.d == 64 ? 1024 : 768)) return true;
+    const bool half = 2LL * a.w >= a.L, most = 4LL * a.w > 3LL * a.L;   // of the keys to each side
+    if (a.d == 64) return a.L <= 1024 || (a.L <= 1216 ? !most : !half);
+    if (n <= 1024) return a.L <= 896 && !half;
+    if (n <= 1280) return true;
+    if (a.L > 1024) return a.L <= 1216 && n <= 2560 && !half;
+    return a.L <= 768 || !most;
+}
+
 // Bands of at most 31 keys take the two-phase form with split probabilities
 // in its in-band phase (64-query workgroups), so that W, and with it R and
 // every reuse that adds R, carries no unaveraged bf16 rounding of its weights.
@@ -1555,7 +1583,7 @@ hipError_t launch_refresh(const AttnLaunch& a, hipStream_t s) {
             default: return hipErrorInvalidValue;
         }
     }
-    if (a.L > 1280) return launch_mode<MODE_REFRESH>(a, s);
+    if (!one_pass_refresh(a)) return launch_mode<MODE_REFRESH>(a, s);
     switch (a.d) {
         case 64: return launch_attn<64, MODE_REFRESH_SPLIT, 1>(a, s);
         case 72: return launch_attn<72, MODE_REFRESH_SPLIT, 1>(a, s);

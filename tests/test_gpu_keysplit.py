@@ -1,8 +1,8 @@
 """GPU parity of the launches that deal a workgroup's key tiles to several
 wavefront groups (at most 512 workgroups of 64 queries and walks of at least 8
 tiles; refreshes of at most 256 workgroups), at the edges of that rule, against
-float64 attention on the same bf16 inputs, and of the refresh forms beside it.  Bars: those of the attention
-parity tests (max 1e-2, mean 1e-3 for unit-variance V; the fp32 residual R
+float64 attention on the same bf16 inputs, and of the one-pass and two-phase
+refresh on both sides of the rule between them.  Bars: those of the attention parity tests (max 1e-2, mean 1e-3 for unit-variance V; the fp32 residual R
 carries the same probability rounding)."""
 import pytest
 import torch
@@ -45,6 +45,14 @@ def _check(name, got, ref):
     (2, 7, 1280, 64, 160),
     (1, 14, 1280, 72, 700),
     (2, 7, 1281, 72, 160),      # two phases
+    # 769 to 1024 workgroups at d = 72, whose one-pass form ends at 896 tokens; bands of most keys
+    (4, 16, 896, 72, 447),
+    (4, 16, 897, 72, 447),
+    (5, 16, 600, 72, 300),
+    (8, 16, 769, 72, 577),      # two phases, one query block per wavefront
+    (8, 16, 769, 72, 576),      # one pass
+    (3, 16, 1100, 72, 137),     # two phases, two query blocks per wavefront
+    (3, 16, 1100, 64, 137),     # one pass
 ])
 @pytest.mark.parametrize("spread", [1.0, 3.0])
 def test_keysplit_vs_fp64(B, H, L, d, w, spread):
