@@ -915,7 +915,7 @@ __device__ __forceinline__ void store_residual(const Params& p, const f32x4 (&o)
 
 // Epilogue of a two-accumulator refresh: W = aw / lw, O from both, each scaled
 // from its own running max to the larger one, R = O - W.
-template <int D, int QB>
+template <int D, int QB, bool ROWS>
 __device__ __forceinline__ void store_split(const Params& p, const Acc<D, QB>& aw, const Acc<D, QB>& ax, size_t head_off,
                                             int qw0, int L, int w, uint16_t* Wl, int lane) {
     using G = Geo<D>;
@@ -947,8 +947,19 @@ __device__ __forceinline__ void store_split(const Params& p, const Acc<D, QB>& a
             res[mb] = o - wv;
             ob[mb] = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
         }
-        store_residual<D>(p, res, Wl, at, rows, lane);
-        store_rows<D>(p, ob, Wl, at, rows, lane);
+        if constexpr (ROWS) {
+            store_residual<D>(p, res, Wl, at, rows, lane);
+            store_rows<D>(p, ob, Wl, at, rows, lane);
+        } else if (qi < L) {
+#pragma unroll
+            for (int mb = 0; mb < G::NDB; ++mb) {
+                const int col = 16 * mb + 4 * (lane >> 4);
+                if (col >= D) continue;
+                const size_t off = head_off + (size_t)qi * D + col;
+                *(f32x4*)(p.Rout + off) = res[mb];
+                for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + off) = ob[mb];
+            }
+        }
     }
 }
 
@@ -956,7 +967,7 @@ __device__ __forceinline__ void store_split(const Params& p, const Acc<D, QB>& a
 // alone; O combines both accumulators, each scaled from its own running max
 // to the larger one.  A query whose band covers every key has no
 // out-of-band score, and its O is then formed exactly as W, so R == 0.
-template <int D, int QB>
+template <int D, int QB, bool ROWS>
 __device__ __forceinline__ void refresh_split(const Params& p, uint16_t* smem, Walk<D, QB, false>& wk, const QFrag<D, QB>& q,
                                               size_t head_off, int ntiles) {
     using G = Geo<D>;
@@ -967,7 +978,7 @@ __device__ __forceinline__ void refresh_split(const Params& p, uint16_t* smem, W
     wait_vm_all();
     __syncthreads();
     wk.run_split(aw, ax, q, 0, ntiles);
-    if (wk.wave_active) store_split<D, QB>(p, aw, ax, head_off, wk.qw0, wk.L, wk.w, smem + (wk.tid >> 6) * 2 * OUT_ELEMS, wk.tid & 63);
+    if (wk.wave_active) store_split<D, QB, ROWS>(p, aw, ax, head_off, wk.qw0, wk.L, wk.w, smem + (wk.tid >> 6) * 2 * OUT_ELEMS, wk.tid & 63);
 }
 
 template <int D, int KMODE, int QB, bool ROWS>
@@ -1098,7 +1109,7 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
     for (int i = NSEG - 1; i >= 0; --i) nxt[i] = s0[i] < s1[i] ? s0[i] : nxt[i + 1];
 
     if constexpr (split_refresh<KMODE>()) {
-        refresh_split<D, QB>(p, smem, wk, q, head_off, ntiles);
+        refresh_split<D, QB, ROWS>(p, smem, wk, q, head_off, ntiles);
         return;
     }
 
@@ -1368,7 +1379,7 @@ attn_keysplit_kernel(Params p) {
         if constexpr (MODE == MODE_REFRESH) add_state<D>(ax, states + (k * NACC + 1) * STATES, lane, p.c);
     }
     if constexpr (MODE == MODE_REFRESH) {
-        store_split<D, 1>(p, acc, ax, head_off, qw0, L, w, smem + STATE0 + (KS - 1) * NACC * STATES + wave * 2 * OUT_ELEMS, lane);
+        store_split<D, 1, true>(p, acc, ax, head_off, qw0, L, w, smem + STATE0 + (KS - 1) * NACC * STATES + wave * 2 * OUT_ELEMS, lane);
     } else {
         const float inv = 1.f / row_sum<D>(acc, 0, r);
         const float* rl = (const float*)(smem + (iters & 1) * G::STAGE_ELEMS) + (wave * 16 + r) * D;
@@ -1458,20 +1469,32 @@ int key_groups(const AttnLaunch& a) {
     return nblocks <= 256 ? 4 : (nblocks <= 512 ? 2 : 1);
 }
 
-// Whether full and window outputs leave as whole lines, through LDS: with
-// several destinations (full (8, 16, 1024, 72) with a cache 56.7 -> 53.6 us,
-// reuse (32, 16, 405, 72) 51.8 -> 47.7), and in launches of 64-query workgroups
-// that write more O than the caches keep beside its inputs (direct and rows on
-// rotating buffers, then on two sets: reuse, 60 MB of O (64, 16, 405, 72) 82.3,
-// 79.0 and 81.7, 79.1 us; 23 MB (16, 16, 700, 64) 39.3, 38.6 and 35.5, 34.9;
-// 19 MB (8, 16, 1024, 72) 34.2, 33.8 and 28.0, 28.5; 4.7 MB (8, 16, 256, 72)
-// 9.84, 10.08 and 9.04, 9.32; (2, 16, 128, 72) 6.13, 6.27 and 5.63, 5.77).  Long
-// walks of 128-query workgroups gain nothing (reuse (2, 16, 8192, 72) 188,
-// 192).  One kernel with both forms in it was slower than either (9.17 us at
-// (8, 16, 256, 72)) and spilled in full attention at d = 72.
-template <int QB>
+// Whether a launch's outputs leave as whole lines, through LDS (time direct over
+// rows, on two sets of buffers and on rotating ones; in MB of O):
+//   - full and window attention, with several destinations (a cache: full (8, 16,
+//     1024, 72) 1.06; reuse (32, 16, 405, 72) 1.09), but not small windows at d =
+//     72 (the conditional half of (8, 16, 256, 72), 2.4 MB, 0.97); with one
+//     destination in launches of 64-query workgroups that write more O than the
+//     caches keep beside its inputs (reuse (64, 16, 405, 72), 60 MB, 1.03 and
+//     1.04; (16, 16, 700, 64), 23 MB, 1.02 and 1.02; (8, 16, 1024, 72), 19 MB,
+//     0.98 and 1.01; (8, 16, 256, 72), 4.7 MB, 0.97 and 0.98; (2, 16, 128, 72)
+//     0.98 and 0.98).  Long walks of 128-query workgroups gain nothing (reuse (2,
+//     16, 8192, 72) 0.98);
+//   - refreshes, whose R passes with them, but at d = 72 for small ones (4 heads
+//     of 40 tokens 0.93, 128 of 100, 1.8 MB, 1.00, 256 of 100, 3.7 MB, 1.04 and
+//     1.08) and, with split probabilities and no cache, to 8 MB (192 heads of 512
+//     0.97 and 0.98, 512 of 256, 19 MB, 0.99 and 1.03).  At d = 64 rows win there
+//     as well (1.02 to 1.06).
+// One kernel with both forms in it was slower than either (9.17 us at (8, 16,
+// 256, 72), 9.05 and 9.11) and spilled in full attention at d = 72.
+template <int D, int MODE, int QB>
 bool store_as_rows(const AttnLaunch& a) {
-    return a.ndst > 1 || (QB == 1 && (size_t)a.B * a.H * a.L * a.d * 2 > (size_t)20 << 20);
+    const size_t kib = (size_t)a.B * a.H * a.L * a.d * 2 >> 10;   // of O
+    if constexpr (MODE == MODE_REFRESH || MODE == MODE_REFRESH_SPLIT || MODE == MODE_REFRESH_FINE)
+        return D != 72 || kib > (MODE == MODE_REFRESH_FINE && a.ndst == 1 ? 8192 : 2048);
+    if (a.ndst > 1) return D != 72 || MODE == MODE_FULL || MODE == MODE_ASC || kib > 2560;
+    const long long keys = MODE == MODE_FULL || a.w >= a.L ? a.L : 2LL * a.w + 1;
+    return QB == 1 && kib > 20 * 1024 && keys <= 400;
 }
 
 template <int D, int MODE, int QB>
@@ -1510,15 +1533,14 @@ hipError_t launch_attn(const AttnLaunch& a, hipStream_t stream) {
             return hipGetLastError();
         }
     }
-    if constexpr (MODE == MODE_FULL || MODE == MODE_WINDOW || MODE == MODE_WINDOW_FINE) {
-        if (store_as_rows<QB>(a)) hipLaunchKernelGGL((attn_kernel<D, MODE, QB, true>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
-        else hipLaunchKernelGGL((attn_kernel<D, MODE, QB, false>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
+    if constexpr (MODE == MODE_REFRESH && QB == 2) {
+        // no registers left for rows at d = 72 (nine spills; 148 -> 152 us at (8,
+        // 16, 1500, 72)), and at d = 64 they gained less than 1%
+        hipLaunchKernelGGL((attn_kernel<D, MODE, QB, false>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
+    } else if (store_as_rows<D, MODE, QB>(a)) {
+        hipLaunchKernelGGL((attn_kernel<D, MODE, QB, true>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
     } else {
-        // ASC has several destinations, and R of a refresh passes through LDS as
-        // well; but the two-phase refresh with two query blocks has no registers
-        // left for it at d = 72 (nine spills; 148 -> 152 us at (8, 16, 1500, 72)),
-        // and at d = 64 it gained less than 1%
-        hipLaunchKernelGGL((attn_kernel<D, MODE, QB, MODE == MODE_ASC || QB == 1>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
+        hipLaunchKernelGGL((attn_kernel<D, MODE, QB, false>), dim3(p.nblocks), dim3(NTHREADS), 0, stream, p);
     }
     return hipGetLastError();
 }

@@ -173,14 +173,14 @@ __device__ __forceinline__ bf16x8 probs(const f32x4 (&s)[NB], int qi, int g, int
 template <int NB, int KMODE>
 constexpr int short_min_waves() { return NB == 2 && KMODE == MODE_WINDOW ? 1 : 4; }
 
-template <int D, int NB, int KMODE>
+template <int D, int NB, int KMODE, bool ROWS_OUT>
 __global__ void __launch_bounds__(SW * 64) __attribute__((amdgpu_waves_per_eu(short_min_waves<NB, KMODE>())))
 short_attn_kernel(SParams p) {
     using G = SGeo<D>;
     constexpr int MODE = KMODE == MODE_ASC ? MODE_FULL : KMODE;
     constexpr int ROWS = 16 * NB;
     // a refresh sends R through LDS as well, as fp32 rows of the same pitch
-    constexpr int WELEMS = ROWS * (MODE == MODE_REFRESH ? 2 * G::OP : G::VP);   // a wavefront's share
+    constexpr int WELEMS = ROWS * (ROWS_OUT && MODE == MODE_REFRESH ? 2 * G::OP : G::VP);   // a wavefront's share
     static_assert(WELEMS >= ROWS * G::VP, "V must fit");
     __shared__ __attribute__((aligned(16))) uint16_t smem[SW * WELEMS];
 
@@ -291,7 +291,7 @@ short_attn_kernel(SParams p) {
         }
     }
 
-    lds_fence();   // V is read: the outputs take its rows
+    if constexpr (ROWS_OUT) lds_fence();   // V is read: the outputs take its rows
     u32x2 ob[NB][G::NDB];   // the output, packed
 #pragma unroll
     for (int qb = 0; qb < NB; ++qb) {
@@ -324,24 +324,31 @@ short_attn_kernel(SParams p) {
             }
             inv[set] = 1.f / l;
         }
+        if (!ROWS_OUT && qi >= L) continue;
 #pragma unroll
         for (int mb = 0; mb < G::NDB; ++mb) {
             // no fma contraction: R must be the difference of the two rounded results
 #pragma clang fp contract(off)
             const int col = 16 * mb + 4 * g;
+            if (!ROWS_OUT && col >= D) continue;
+            const size_t at = off + (size_t)qi * D + col;
             const f32x4 ov = o[0][mb] * inv[0];
             f32x4 out = ov;
             if constexpr (MODE == MODE_REFRESH) {
                 const f32x4 res = ov - o[NSET - 1][mb] * inv[NSET - 1];
-                if (qi < L && col < D) *(f32x4*)((float*)Vl + qi * G::OP + col) = res;
+                if constexpr (!ROWS_OUT) *(f32x4*)(p.Rout + at) = res;
+                else if (qi < L && col < D) *(f32x4*)((float*)Vl + qi * G::OP + col) = res;
             }
             if constexpr (MODE == MODE_WINDOW) {
                 if (p.Rin) out = ov + rin[qb][mb];
             }
             ob[qb][mb] = u32x2{pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3])};
+            if constexpr (!ROWS_OUT)
+                for (int di = 0; di < p.ndst; ++di) *(u32x2*)(p.dst[di] + at) = ob[qb][mb];
         }
     }
 
+    if constexpr (!ROWS_OUT) return;
     if constexpr (MODE == MODE_REFRESH) {
         lds_fence();
         constexpr int N4 = D / 4;
@@ -380,6 +387,21 @@ short_attn_kernel(SParams p) {
     }
 }
 
+// Whether the outputs leave through LDS.  The pass costs a small launch its
+// latency where there is most of it, R beside O or a residual to add (time direct
+// over rows): refresh, at d = 72 512 sequences of 32 tokens (2.4 MB of O) 0.96,
+// 896 (4.1) 1.07, 512 of 7 (0.5) 0.96, 768 of 16 (1.8) 1.01; at d = 64 512 of 24
+// (1.6) 0.96, 768 (2.4) 1.01, and 512 of 16 and of 32 1.03; windows of two blocks
+// at d = 72 without a cache, 3072 of 24 (10.6) 0.95 to 0.99, 5120 (17.7) 0.97 to
+// 1.06.  Elsewhere rows win at every size (full, 64 sequences of (16, 64) 1.08).
+template <int D, int NB, int MODE>
+bool short_rows(const AttnLaunch& a) {
+    const size_t kib = (size_t)a.B * a.H * a.L * a.d * 2 >> 10;   // of O
+    if constexpr (MODE == MODE_REFRESH) return D == 72 ? kib > 2048 : (kib > 1536 || a.L % 16 == 0);
+    if constexpr (MODE == MODE_WINDOW && NB == 2 && D == 72) return a.ndst > 1 || kib > 12 * 1024;
+    return true;
+}
+
 template <int D, int NB, int MODE>
 hipError_t launch_short_attn(const AttnLaunch& a, hipStream_t stream) {
     SParams p{};
@@ -398,7 +420,10 @@ hipError_t launch_short_attn(const AttnLaunch& a, hipStream_t stream) {
     p.L = a.L;
     p.w = a.w;
     p.c = (float)(1.4426950408889634 / __builtin_sqrt((double)D));
-    hipLaunchKernelGGL((short_attn_kernel<D, NB, MODE>), dim3((unsigned)nblocks), dim3(SW * 64), 0, stream, p);
+    if (short_rows<D, NB, MODE>(a))
+        hipLaunchKernelGGL((short_attn_kernel<D, NB, MODE, true>), dim3((unsigned)nblocks), dim3(SW * 64), 0, stream, p);
+    else
+        hipLaunchKernelGGL((short_attn_kernel<D, NB, MODE, false>), dim3((unsigned)nblocks), dim3(SW * 64), 0, stream, p);
     return hipGetLastError();
 }
 

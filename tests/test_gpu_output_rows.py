@@ -1,6 +1,6 @@
-"""The outputs that leave as rows through LDS: every number of valid rows in a
-wavefront's last block, both head dims, one to four destinations, against
-float64 attention.  Bars: those of the attention parity tests (max 1e-2, mean
+"""The outputs, which leave as rows through LDS or straight from the registers:
+every number of valid rows in a wavefront's last block, both head dims, one to
+four destinations, against float64 attention.  Bars: those of the attention parity tests (max 1e-2, mean
 1e-3 for unit-variance V; W, O and R of a refresh carry the same rounding)."""
 import pytest
 import torch
@@ -14,11 +14,11 @@ pytestmark = pytest.mark.gpu
 
 # short kernel (one and two blocks, whole and ragged), 64-query workgroups with
 # and without key groups, 128-query workgroups; the second block of a wavefront
-# whole, of one row and empty; more than 20 MiB of O, where one destination of a
-# short walk is stored like several
+# whole, of one row and empty; both sides of the sizes from which outputs leave
+# through LDS (2, 8, 12 and 20 MiB of O, with and without a cache)
 @pytest.mark.parametrize("B,H,L", [(6, 3, 1), (4, 5, 9), (2, 9, 16), (2, 3, 17), (4, 7, 32), (2, 3, 33), (2, 2, 79), (2, 16, 320),
                                    (20, 16, 273), (20, 16, 384), (20, 16, 391), (2, 80, 1400),
-                                   (32, 16, 405)])
+                                   (32, 16, 405), (40, 16, 32), (200, 16, 31), (20, 16, 79), (48, 16, 79)])
 @pytest.mark.parametrize("d", [64, 72])
 def test_output_rows(B, H, L, d):
     dev = torch.device("cuda")
