@@ -25,21 +25,46 @@ def _check(name, got, ref):
     assert not bad.any(), f"{name}: {int(bad.sum())} outputs off, max abs {float(err.max()):.3e}"
 
 
-# (B, H, L, d): the tile shape of the QKV projection, then of the output projection
-@pytest.mark.parametrize("B,H,L,d", [
-    (1, 2, 1, 64),          # one token, K = 128 (two k-tiles): 64 x 64 ring
-    (3, 2, 37, 64),         # ragged token tile, tokens of one tile in several batch entries
-    (5, 16, 63, 72),        # 320 tokens of 1152 features: 128 x 128 ring / 64 x 64 ring
-    (2, 6, 701, 64),        # K = 384, features not a multiple of 192 in the output projection
-    (3, 16, 683, 72),       # 128 x 128 stream (one round, ragged) / 128 x 128 ring
-    (2, 16, 2050, 72),      # 128 x 128 stream / 128 x 128 stream, last token tile of 4
-    (1, 2, 170001, 64),     # K = 128 over many tiles per workgroup (192 x 256 and 128 x 128)
-    (1, 6, 60003, 64),      # K = 384, output features a multiple of 192, many tiles, ragged
-    (2, 10, 9001, 64),      # K = 640: 640 features leave a feature tile of 64 in 192-wide tiles
-    (4000, 16, 2, 72),      # a new batch entry every other token
+def _route(N, M):
+    """The tile shape that the library's rule gives N output features of M
+    tokens (features x tokens of a workgroup, "ring" or "stream")."""
+    tiles = lambda f, t: -(-N // f) * -(-M // t)  # noqa: E731
+    n128, n192 = tiles(128, 128), tiles(192, 256)
+    if tiles(64, 64) <= 256:
+        return "64x64 ring"
+    if n128 <= 256:
+        return "128x128 ring"
+    last = n128 % 512
+    rounds = 100 * (n128 // 512) + (0 if last == 0 else 65 if last <= 256 else 100)
+    return "192x256 stream" if 125 * -(-n192 // 256) < rounds else "128x128 stream"
+
+
+R64, R128, S128, S192 = "64x64 ring", "128x128 ring", "128x128 stream", "192x256 stream"
+
+
+# (B, H, L, d), the tile shape of the QKV projection, then of the output
+# projection.  A QKV projection's 3C features are a multiple of 192 (C is one of
+# 128); output features need not be.
+@pytest.mark.parametrize("B,H,L,d,qkv,out", [
+    (1, 2, 1, 64, R64, R64),            # one token, K = 128 (two k-tiles)
+    (3, 2, 37, 64, R64, R64),           # ragged token tile, tokens of one tile in several batch entries
+    (5, 16, 63, 72, R128, R64),
+    (2, 6, 701, 64, R128, R64),         # K = 384
+    (3, 16, 683, 72, S128, R128),       # one round, ragged
+    (2, 16, 2050, 72, S128, S128),      # last token tile of 4
+    (1, 2, 170001, 64, S192, S128),     # K = 128 over many tiles per workgroup
+    (1, 6, 60003, 64, S192, S192),      # K = 384, output features a multiple of 192, many tiles, ragged
+    (2, 10, 9001, 64, S192, S128),      # K = 640
+    (4000, 16, 2, 72, S128, S192),      # a new batch entry every other token
+    # output features not a multiple of 192: a last feature tile of 64 (whole and
+    # ragged last token tile) and of 128, with further tiles of the same workgroup behind it
+    (2, 16, 16384, 64, S192, S192),
+    (2, 16, 16350, 64, S192, S192),
+    (1, 8, 65003, 64, S192, S192),
 ])
 @pytest.mark.parametrize("bias", [True, False])
-def test_projection_tile_edges(B, H, L, d, bias):
+def test_projection_tile_edges(B, H, L, d, qkv, out, bias):
+    assert (_route(3 * H * d, B * L), _route(H * d, B * L)) == (qkv, out), "not the tile shapes this case is for"
     C = H * d
     g = torch.Generator(device="cuda")
     g.manual_seed(B + 7 * L)
