@@ -2,7 +2,8 @@
 wavefront groups (at most 512 workgroups of 64 queries and walks of at least 8
 tiles; refreshes of at most 256 workgroups), at the edges of that rule, against
 float64 attention on the same bf16 inputs, and of the one-pass and two-phase
-refresh on both sides of the rule between them.  Bars: those of the attention parity tests (max 1e-2, mean 1e-3 for unit-variance V; the fp32 residual R
+refresh on both sides of the rule between them.  Bars: those of the attention
+parity tests (max 1e-2, mean 1e-3 for unit-variance V; the fp32 residual R
 carries the same probability rounding)."""
 import pytest
 import torch

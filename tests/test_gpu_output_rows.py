@@ -1,7 +1,8 @@
 """The outputs, which leave as rows through LDS or straight from the registers:
 every number of valid rows in a wavefront's last block, both head dims, one to
-four destinations, against float64 attention.  Bars: those of the attention parity tests (max 1e-2, mean
-1e-3 for unit-variance V; W, O and R of a refresh carry the same rounding)."""
+four destinations, against float64 attention.  Bars: those of the attention
+parity tests (max 1e-2, mean 1e-3 for unit-variance V; W, O and R of a refresh
+carry the same rounding)."""
 import pytest
 import torch
 
@@ -42,7 +43,7 @@ def test_output_rows(B, H, L, d):
         _check(f"{name} O", O.t[:n].float(), full[:n])
         if half:
             assert torch.equal(O.t[n:], O.t[:n]), name
-        assert torch.equal(C.t, O.t) or bool((C.t == -7).all()), name
+        assert torch.equal(C.t, O.t), name   # every one of these codes writes the cache
         assert torch.equal(one, O.t), name
         if res:
             _check(f"{name} R", R.t[:n], (full - win)[:n])

@@ -133,10 +133,11 @@ def test_kernels_vs_oracle(B, H, L, d, w):
 # Launches with short tile walks, or with at most 256 workgroups of 128
 # queries, run 64-query workgroups (one 16-query block per wavefront), the
 # rest 128-query workgroups; these shapes sit on both sides of each switch:
-# full attention at L = 256, refresh at L = 512 (one pass with two
-# accumulators up to there) and at L = 1024, window attention at a band of
-# 1280 keys (w = 639 / 640), and the workgroup count (B*H*ceil(L/128) = 256
-# against 288 and 384).
+# full attention at L = 256, window attention at a band of 1280 keys (w = 639 /
+# 640), and the workgroup count (B*H*ceil(L/128) = 256 against 288 and 384).
+# With B*H <= 2 every refresh deals its keys to two wavefront groups; the switch
+# between one and two phases of larger launches has its shapes in
+# test_gpu_keysplit.
 ROUTE_SHAPES = [
     (1, 16, 2048, 72, 256),
     (2, 16, 1025, 72, 100),
