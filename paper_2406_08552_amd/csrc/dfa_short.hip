@@ -170,11 +170,17 @@ __device__ __forceinline__ bf16x8 probs(const f32x4 (&s)[NB], int qi, int g, int
 // against the unconstrained build: window attention at L = 16 15% faster
 // (132 -> 76 VGPRs, three -> six wavefronts per SIMD), L = 12 5-10% faster in
 // every mode, the L = 32 refresh 8% faster; the L = 32 window 11% slower.
-template <int NB, int KMODE>
-constexpr int short_min_waves() { return NB == 2 && KMODE == MODE_WINDOW ? 1 : 4; }
+// Two kernels whose outputs leave as rows keep the wavefronts that they have with
+// direct stores: the one-block window at d = 64 eight (65 -> 64 VGPRs) and the
+// two-block full attention at d = 72 five (98 -> 96).
+template <int D, int NB, int KMODE>
+constexpr int short_min_waves() {
+    if (KMODE == MODE_WINDOW) return NB == 2 ? 1 : (D == 64 ? 8 : 4);
+    return KMODE != MODE_REFRESH && NB == 2 ? 5 : 4;
+}
 
 template <int D, int NB, int KMODE, bool ROWS_OUT>
-__global__ void __launch_bounds__(SW * 64) __attribute__((amdgpu_waves_per_eu(short_min_waves<NB, KMODE>())))
+__global__ void __launch_bounds__(SW * 64) __attribute__((amdgpu_waves_per_eu(short_min_waves<D, NB, KMODE>())))
 short_attn_kernel(SParams p) {
     using G = SGeo<D>;
     constexpr int MODE = KMODE == MODE_ASC ? MODE_FULL : KMODE;
@@ -387,20 +393,42 @@ short_attn_kernel(SParams p) {
     }
 }
 
-// Whether the outputs leave through LDS.  The pass costs a small launch its
-// latency where there is most of it, R beside O or a residual to add (time direct
-// over rows): refresh, at d = 72 512 sequences of 32 tokens (2.4 MB of O) 0.96,
-// 896 (4.1) 1.07, 512 of 7 (0.5) 0.96, 768 of 16 (1.8) 1.01; at d = 64 512 of 24
-// (1.6) 0.96, 768 (2.4) 1.01, and 512 of 16 and of 32 1.03; windows of two blocks
-// at d = 72 without a cache, 3072 of 24 (10.6) 0.95 to 0.99, 5120 (17.7) 0.97 to
-// 1.06.  Elsewhere rows win at every size (full, 64 sequences of (16, 64) 1.08).
+// Whether the outputs leave through LDS (time direct over rows; in KiB of O,
+// from 3528 launches of 1 to 32 tokens).  Rows win at every size with several
+// destinations and in full attention (one destination, 1.01 to 1.1 on average,
+// two 1.05 to 1.3, four 1.1 to 1.7).  The pass costs a small launch its latency
+// where there is most of it, R beside O or a residual to add:
+//   - refresh, one destination: at d = 72 to 1024 0.89, to 2048 0.92, to 4096 0.99
+//     (768 sequences of 16 1.01, 688 of 22 0.95), beyond 1.05 to 1.4; at d = 64 to
+//     1024 0.95, to 2048 1.04 in one block and 0.96 in two, beyond 1.03 to 1.5, and
+//     16 or 32 tokens 1.03 and 0.99 below;
+//   - refresh with a cache or both halves: at d = 72 two destinations to 1024 0.94,
+//     to 2048 0.99, beyond 1.06 to 1.6, four 0.98 below 1024 in one block and 1.02
+//     in two; at d = 64 below 1024 two 0.95 to 7 tokens, 1.0 to 1.1 from 8 on, four
+//     1.1 to 1.3;
+//   - windows of two blocks, one destination: at d = 72 to 22 MiB 0.95, beyond 1.05;
+//     at d = 64 to 16 MiB 0.99, beyond 1.03.
 template <int D, int NB, int MODE>
 bool short_rows(const AttnLaunch& a) {
     const size_t kib = (size_t)a.B * a.H * a.L * a.d * 2 >> 10;   // of O
-    if constexpr (MODE == MODE_REFRESH) return D == 72 ? kib > 2048 : (kib > 1536 || a.L % 16 == 0);
-    if constexpr (MODE == MODE_WINDOW && NB == 2 && D == 72) return a.ndst > 1 || kib > 12 * 1024;
+    if constexpr (MODE == MODE_REFRESH && D == 72) {
+        if (a.ndst == 4) return NB == 2 || kib > 1024;
+        return kib > (a.ndst == 2 ? 1536 : (NB == 1 ? 2048 : 3072));
+    }
+    if constexpr (MODE == MODE_REFRESH)
+        return a.ndst == 4 || (a.ndst == 2 && a.L >= 8) || kib > (NB == 1 ? 1024 : 2048) || a.L % 16 == 0;
+    if constexpr (MODE == MODE_WINDOW && NB == 2) return a.ndst > 1 || kib > (D == 72 ? 22 : 16) * 1024;
     return true;
 }
+
+// Bytes of a call's O from which it is stored without allocation, like the cache.
+// Below, the projection that reads it gains more than the call loses; so much of
+// it does not stay in the caches until then.  Call and call with projection,
+// without over with, by MiB of O: full to 45 0.88 to 0.95 and 1.04 to 1.13, from
+// 64 on 0.96 and 0.96; reuse to 32 0.95 and 1.05, from 64 on 0.96 and 0.97; refresh
+// and both halves to 64 0.84 to 1.0 and 1.01 to 1.07, from 90 on 0.96 to 1.0 and
+// 0.97 to 1.03.  (Longer sequences: level from 128 MiB on.)
+constexpr size_t SHORT_O_CACHED = (size_t)80 << 20;
 
 template <int D, int NB, int MODE>
 hipError_t launch_short_attn(const AttnLaunch& a, hipStream_t stream) {
@@ -411,7 +439,7 @@ hipError_t launch_short_attn(const AttnLaunch& a, hipStream_t stream) {
     p.Rin = (const float*)a.Rin;
     p.Rout = (float*)a.Rout;
     p.ndst = a.ndst;
-    p.nout = a.nout;
+    p.nout = (size_t)a.Bcall * a.H * a.L * a.d * 2 >= SHORT_O_CACHED ? 0 : a.nout;
     for (int i = 0; i < 4; ++i) p.dst[i] = (uint16_t*)(i < a.ndst ? a.dst[i] : nullptr);
     const long long nseq = (long long)a.B * a.H;
     const long long nblocks = (nseq + SW - 1) / SW;

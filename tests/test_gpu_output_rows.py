@@ -16,10 +16,12 @@ pytestmark = pytest.mark.gpu
 # short kernel (one and two blocks, whole and ragged), 64-query workgroups with
 # and without key groups, 128-query workgroups; the second block of a wavefront
 # whole, of one row and empty; both sides of the sizes from which outputs leave
-# through LDS (2, 8, 12 and 20 MiB of O, with and without a cache)
+# through LDS (1 to 22 MiB of O, with and without a cache), and more than 80 MiB
+# of O in short sequences (stored without allocation)
 @pytest.mark.parametrize("B,H,L", [(6, 3, 1), (4, 5, 9), (2, 9, 16), (2, 3, 17), (4, 7, 32), (2, 3, 33), (2, 2, 79), (2, 16, 320),
                                    (20, 16, 273), (20, 16, 384), (20, 16, 391), (2, 80, 1400),
-                                   (32, 16, 405), (40, 16, 32), (200, 16, 31), (20, 16, 79), (48, 16, 79)])
+                                   (32, 16, 405), (40, 16, 32), (200, 16, 31), (20, 16, 79), (48, 16, 79),
+                                   (24, 16, 31), (40, 16, 31), (200, 16, 20), (320, 16, 31), (1400, 16, 31), (14, 16, 79), (12, 16, 45)])
 @pytest.mark.parametrize("d", [64, 72])
 def test_output_rows(B, H, L, d):
     dev = torch.device("cuda")
