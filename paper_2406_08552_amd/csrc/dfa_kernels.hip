@@ -751,7 +751,7 @@ struct Walk {
             // fragment is read once for both: against a mask and a PV pass of
             // its own for each, 79.1 -> 75 us at (32, 16, 405, 72), 28.9 ->
             // 24.1 us at (8, 16, 500, 64), where registers also fell from 154
-            // to 125 and a fourth wavefront per SIMD fits.
+            // to 127 and a fourth wavefront per SIMD fits.
             Tile<QB> X;
             if (ragged) mask_tile<MASK_KEYS>(S, r, g, qw0, k0, L, w);
             split_tile(S, X, r, g, qw0, k0, L, w);
@@ -1023,8 +1023,9 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
         }
     }
 
-    // Q fragments, zero beyond L and beyond d (in line: called, the window walk of
-    // 512 workgroups at (8, 16, 256, 72) measured 9.06 us, in line 9.01)
+    // Q fragments, zero beyond L and beyond d.  load_q in line: called, the window
+    // walk of 512 workgroups at (8, 16, 256, 72) takes 9.28 us, in line 9.25 (31
+    // rounds in turn, twice; 9.06 and 9.01 on another card).
     QFrag<D, QB> q;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -1218,7 +1219,7 @@ __device__ __forceinline__ void attn_body(const Params& p, uint16_t* smem) {
 // Three waves per SIMD with two query blocks per wavefront (register budget
 // 168), four with one (budget 128): the MFMA work of one wavefront overlaps the
 // softmax arithmetic of the others.  The two-accumulator refresh fits four at
-// d = 64 (125 registers; 27.0 -> 23.9 us at (8, 16, 500, 64)); at d = 72 it
+// d = 64 (127 registers; 27.0 -> 23.9 us at (8, 16, 500, 64)); at d = 72 it
 // needs 143, and in 128 it spills (77.4 -> 82.1 us at (32, 16, 405, 72)).
 template <int D, int QB, int KMODE>
 constexpr int waves_per_simd() { return QB == 1 && (D == 64 || !split_refresh<KMODE>()) ? 4 : 3; }
@@ -1470,29 +1471,33 @@ int key_groups(const AttnLaunch& a) {
 }
 
 // Whether a launch's outputs leave as whole lines, through LDS (time direct over
-// rows, on two sets of buffers and on rotating ones; in MB of O):
-//   - full and window attention, with several destinations (a cache: full (8, 16,
-//     1024, 72) 1.06; reuse (32, 16, 405, 72) 1.09), but not small windows at d =
-//     72 (the conditional half of (8, 16, 256, 72), 2.4 MB, 0.97); with one
-//     destination in launches of 64-query workgroups that write more O than the
-//     caches keep beside its inputs (reuse (64, 16, 405, 72), 60 MB, 1.03 and
-//     1.04; (16, 16, 700, 64), 23 MB, 1.02 and 1.02; (8, 16, 1024, 72), 19 MB,
-//     0.98 and 1.01; (8, 16, 256, 72), 4.7 MB, 0.97 and 0.98; (2, 16, 128, 72)
-//     0.98 and 0.98).  Long walks of 128-query workgroups gain nothing (reuse (2,
-//     16, 8192, 72) 0.98);
-//   - refreshes, whose R passes with them, but at d = 72 for small ones (4 heads
-//     of 40 tokens 0.93, 128 of 100, 1.8 MB, 1.00, 256 of 100, 3.7 MB, 1.04 and
-//     1.08) and, with split probabilities and no cache, to 8 MB (192 heads of 512
-//     0.97 and 0.98, 512 of 256, 19 MB, 0.99 and 1.03).  At d = 64 rows win there
-//     as well (1.02 to 1.06).
+// rows, on two sets of buffers, 2160 launches of 33 to 4096 tokens; in MB of O):
+//   - full and window attention with several destinations (a cache, both halves;
+//     1.02 to 1.5), but not small windows of 64-query workgroups at d = 72 (two
+//     destinations to 2.6 MB 0.98, above 1.01 to 1.15, four to 2 MB 0.98 to 1.00,
+//     above 1.05 to 1.3; full attention there 1.00 and 1.01);
+//   - with one destination, full attention at d = 64 in 64-query workgroups (1.02
+//     to 1.09), and other launches of these that write more O than the caches
+//     keep beside its inputs (reuse (64, 16, 405, 72), 60 MB, 1.03; (16, 16, 700,
+//     64), 23 MB, 1.02; (8, 16, 1024, 72), 19 MB, 0.98 and 1.01; (8, 16, 256,
+//     72), 4.7 MB, 0.97 and 0.98; (2, 16, 128, 72) 0.98).  Long walks of 128-query
+//     workgroups gain nothing (reuse (2, 16, 8192, 72) 0.98);
+//   - refreshes, whose R passes with them, but at d = 72 for small ones (one
+//     or two destinations to 2 MB: 4 heads of 40 tokens 0.93, 128 of 100, 1.8 MB,
+//     1.00, 256 of 100, 3.7 MB, 1.04 and 1.08; four to 1 MB 1.00, to 2 MB 1.02 to
+//     1.09)
+//     and, with split probabilities, one destination to 8 MB (192 heads of 512
+//     0.97 and 0.98, 512 of 256, 19 MB, 0.99 and 1.03), two to 3 MB (0.96 to 0.99,
+//     above 1.02 to 1.15).  At d = 64 rows win there as well (1.02 to 1.3).
 // One kernel with both forms in it was slower than either (9.17 us at (8, 16,
 // 256, 72), 9.05 and 9.11) and spilled in full attention at d = 72.
 template <int D, int MODE, int QB>
 bool store_as_rows(const AttnLaunch& a) {
     const size_t kib = (size_t)a.B * a.H * a.L * a.d * 2 >> 10;   // of O
-    if constexpr (MODE == MODE_REFRESH || MODE == MODE_REFRESH_SPLIT || MODE == MODE_REFRESH_FINE)
-        return D != 72 || kib > (MODE == MODE_REFRESH_FINE && a.ndst == 1 ? 8192 : 2048);
-    if (a.ndst > 1) return D != 72 || MODE == MODE_FULL || MODE == MODE_ASC || kib > 2560;
+    if constexpr (MODE == MODE_REFRESH_FINE) return D != 72 || kib > (a.ndst == 1 ? 8192 : a.ndst == 2 ? 3072 : 1024);
+    if constexpr (MODE == MODE_REFRESH || MODE == MODE_REFRESH_SPLIT) return D != 72 || kib > (a.ndst == 4 ? 1024 : 2048);
+    if (a.ndst > 1) return D != 72 || QB == 2 || MODE == MODE_FULL || MODE == MODE_ASC || kib > (a.ndst == 2 ? 2560 : 2048);
+    if constexpr (MODE == MODE_FULL && D == 64 && QB == 1) return true;
     const long long keys = MODE == MODE_FULL || a.w >= a.L ? a.L : 2LL * a.w + 1;
     return QB == 1 && kib > 20 * 1024 && keys <= 400;
 }
@@ -1564,22 +1569,24 @@ hipError_t launch_asc(const AttnLaunch& a, hipStream_t s) { return launch_mode<M
 // Whether a refresh takes the one-pass two-accumulator form: where band-edge
 // tiles, which the two-phase form visits twice, are a large part of the walk.
 // Three things set its limit (times of two phases over one in brackets, B * H *
-// ceil(L / 64) = n workgroups of 64 queries; 1296 launches of 640 to 1280 tokens
+// ceil(L / 64) = n workgroups of 64 queries; 2766 launches of 513 to 1400 tokens
 // were measured in both forms, of which the rule is never more than 5% slower
 // than two phases, which took all of them beyond 512 tokens before, and 11%
 // faster on average):
 //   - rounds.  One pass holds 1024 workgroups at once at d = 64, 768 at d = 72
 //     (three wavefronts per SIMD); two phases hold 1024, and beyond 1024 tokens
 //     768 of twice the queries, which leaves half a round of n <= 768 idle.
-//     d = 72: n = 576 of 1100 tokens (1.4 to 1.54), n = 832 of 800 (1.05, 0.98),
-//     1024 of 1024 (1.00 to 0.94), 1152 of 1024 (1.1 to 1.17), 1280 of 1280 (1.06
-//     to 1.14);
+//     d = 72: n = 576 of 1100 tokens (1.4 to 1.54), 769 to 1024 (1.03 to 1.10 with
+//     w = L / 8, 0.92 to 0.99 from half the keys on), 1152 of 1024 (1.1 to 1.25),
+//     1280 of 1280 (1.06 to 1.19);
 //   - the band.  Nearly all keys in it leave two phases little more than full
 //     attention's work: d = 72, n = 2880 of 900 tokens, w = 675 (1.04), w = 898
 //     (0.98); beyond 1024 tokens from half the keys on, n = 2432 of 1216, w = 405
 //     (1.08), w = 608 (1.00), w = 1214 (0.88);
-//   - K/V copies per query, which two query blocks per wavefront halve: 1216
-//     tokens, w = 152, n = 2432 (1.10), 7296 (1.00); d = 64 (1.17) and (1.10).
+//   - K/V copies per query, which two query blocks per wavefront halve: d = 72
+//     beyond 1024 tokens, w = L / 8, n = 1281 to 2560 (1.01 to 1.30), to 5000 (1.01
+//     to 1.2), to 10000 (0.96 to 1.04); d = 64 (1.06 to 1.3), (1.07 to 1.26) and
+//     (1.04 to 1.14).
 // As with the key groups, the whole call's batch decides.
 bool one_pass_refresh(const AttnLaunch& a) {
     if (a.L <= 512) return true;
@@ -1588,9 +1595,9 @@ bool one_pass_refresh(const AttnLaunch& a) {
     if (n <= (a.d == 64 ? 1024 : 768)) return true;
     const bool half = 2LL * a.w >= a.L, most = 4LL * a.w > 3LL * a.L;   // of the keys to each side
     if (a.d == 64) return a.L <= 1024 || (a.L <= 1216 ? !most : !half);
-    if (n <= 1024) return a.L <= 896 && !half;
+    if (n <= 1024) return 8LL * a.w <= 3LL * a.L;
     if (n <= 1280) return true;
-    if (a.L > 1024) return a.L <= 1216 && n <= 2560 && !half;
+    if (a.L > 1024) return n <= 5000 && !half;
     return a.L <= 768 || !most;
 }
 

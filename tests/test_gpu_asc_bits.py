@@ -21,7 +21,8 @@ SHAPES = [
     (2, 12, 1300, 72, 400),     # 504, 264
     (2, 9, 1500, 64, 700),      # 432, 216: two-phase refresh of the whole call, half of it 216
     (4, 16, 256, 72, 32),       # 256, 128
-    (4, 13, 1000, 72, 125),     # 832, 416: a two-phase refresh, of which the half alone would be one-pass
+    (4, 13, 1000, 72, 125),     # 832, 416
+    (4, 13, 1000, 72, 500),     # a two-phase refresh, of which the half alone would be one-pass
     (2, 3, 65, 72, 20),         # 12, 12
     (6, 5, 16, 72, 2),          # short sequences
 ]

@@ -46,14 +46,21 @@ def _check(name, got, ref):
     (2, 7, 1280, 64, 160),
     (1, 14, 1280, 72, 700),
     (2, 7, 1281, 72, 160),      # two phases
-    # 769 to 1024 workgroups at d = 72, whose one-pass form ends at 896 tokens; bands of most keys
-    (4, 16, 896, 72, 447),
+    # 769 to 1024 workgroups at d = 72: one pass up to a band of 3/8 of the keys to each side
+    (4, 16, 896, 72, 336),
+    (4, 16, 896, 72, 337),
     (4, 16, 897, 72, 447),
     (5, 16, 600, 72, 300),
-    (8, 16, 769, 72, 577),      # two phases, one query block per wavefront
-    (8, 16, 769, 72, 576),      # one pass
-    (3, 16, 1100, 72, 137),     # two phases, two query blocks per wavefront
+    (3, 16, 1100, 72, 137),     # one pass
+    (3, 16, 1100, 72, 600),     # two phases, two query blocks per wavefront
     (3, 16, 1100, 64, 137),     # one pass
+    # more workgroups: bands of 3/4 of the keys, and of half of them beyond 1024 tokens, in two phases
+    (8, 16, 769, 72, 577),      # one query block per wavefront
+    (8, 16, 769, 72, 576),      # one pass
+    (4, 18, 1100, 72, 549),     # one pass
+    (4, 18, 1100, 72, 550),
+    (1, 277, 1100, 72, 137),    # 4986: one pass
+    (1, 278, 1100, 72, 137),    # 5004: two phases
 ])
 @pytest.mark.parametrize("spread", [1.0, 3.0])
 def test_keysplit_vs_fp64(B, H, L, d, w, spread):
