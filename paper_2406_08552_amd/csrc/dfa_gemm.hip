@@ -32,9 +32,9 @@
 //
 // What bounds it, at 32768 tokens x 1152 features (PixArt-Sigma at 2048 px):
 // in a steady stream of launches the chip's power limit (the shader clock
-// falls to about 1.8 GHz with N(0, 1) data and stays at 2.37 GHz with zeros,
-// same instructions), then the output stores and the copies' latency at each
-// k-tile's barrier; LDS bank conflicts are zero.  Measured there, against the
+// falls with N(0, 1) data, where zeros, same instructions, keep it), then the
+// output stores and the copies' latency at each k-tile's barrier; LDS bank
+// conflicts take 1% of the cycles.  Measured there, against the
 // kernels this replaced (whose partial vmcnt wait the barrier's own fence
 // undid, and whose epilogue waited for each of its 32 bias loads in turn):
 // QKV projection 337 -> 277 us, output projection 133 -> 108 us; at 2048
